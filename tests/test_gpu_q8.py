@@ -189,3 +189,24 @@ def test_q8_batched_llama3_8b_down_proj_full_size(M):
     assert np.array_equal(codes.cpu().numpy()[rows], r.codes)
     ref = O.matmul_q8(a.q, a.d, r.codes, r.scales, None, len(rows), spec.cols, 32, 4)
     assert_q8_close(g_y.t, ref, rows, f"q8 batched down_proj M={M}")
+
+
+# ---------------------------------------------------------------------------
+# Tiles of the several-token kernel (q8_gemm.hip): 32x32, 32x64, 64x64, 64x128 and 128x128
+# outputs, chosen by how many of each cover M x N.
+# ---------------------------------------------------------------------------
+
+@pytest.mark.parametrize("M,N,K", [
+    (3, 33, 544),        # 32x32: a ragged tile both ways, two 512-deep stages, the second one block
+    (31, 8225, 288),     # 32x64: the last tile one column; two 256-deep stages, the second one block
+    (65, 8161, 800),     # 64x64: two token tiles, the second one row; four stages, the last one block
+    (129, 10400, 256),   # 64x128: three token tiles; exactly one stage
+    (255, 14305, 1056),  # 128x128: two token tiles, the second short of a row; five stages
+])
+@pytest.mark.parametrize("q", [2, 3, 4])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_matmul_q8_tiles(M, N, K, q, mode):
+    spec = synth.WeightSpec(N, K, nu=5.0, scale=0.02, outlier_frac=0.001, seed=M + q)
+    w = O.bf16_bits_to_f32(synth.weights(spec))
+    check_q8_matmul(w, act_bits(M, K, seed=M + mode), 32, q, mode, rows_idx=sample_rows(N, n=40, seed=q),
+                    tag=f"tiles {M}x{N}x{K} q={q} m={mode}")
