@@ -1,4 +1,4 @@
-// Decode GEMV (M = 1) over packed few-bit weights, plus the binary32 matmul.
+// Decode GEMV (M = 1, 2) over packed few-bit weights.
 //
 // App. B.3 of the paper: with W[n,k] ~ s[n,b] (u[n,k] - o[n,b]) in group b,
 //   y[n] = sum_b s[n,b] * ( sum_{k in b} x[k] u[n,k]  -  o[n,b] sum_{k in b} x[k] ).
@@ -38,13 +38,6 @@ template <int Q>
 struct Block {
   uint32_t d[Q];
 };
-
-template <int Q>
-__device__ __forceinline__ Block<Q> load_block(const uint8_t* p) {
-  Block<Q> b;
-  load_block_codes<Q>(p, b.d);
-  return b;
-}
 
 // Activation pairs laid out to match the code pairs produced by block_dot.
 // For q = 4 and q = 3 every 8 weights form pairs (e_j, e_{j+4}); for q = 2
@@ -637,54 +630,6 @@ bool gemv_stat_dispatch(const uint16_t* x, const uint8_t* codes, const uint16_t*
   return true;
 }
 
-// ---------------------------------------------------------------------------
-// Binary32 matmul: x[M,K] fp32, y[M,N] fp32.  One wavefront per (row n, 4 tokens);
-// each lane dequantizes whole 32-weight blocks exactly in fp32.
-// ---------------------------------------------------------------------------
-
-constexpr int kF32Tokens = 4;
-
-template <int Q, int G, int META>
-__global__ __launch_bounds__(256) void matmul_f32_kernel(const float* __restrict__ x, int M,
-                                                         const uint8_t* __restrict__ codes,
-                                                         const uint16_t* __restrict__ scales,
-                                                         const void* __restrict__ meta, int N,
-                                                         int K, float* __restrict__ y) {
-  const int lane = threadIdx.x & 63;
-  const int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int m0 = blockIdx.y * kF32Tokens;
-  if (n >= N) return;
-  const int nblk = K / 32;
-  const int64_t row_bytes = (int64_t)K * Q / 8;
-  float acc[kF32Tokens] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int j = lane; j < nblk; j += 64) {
-    const Block<Q> b = load_block<Q>(codes + n * row_bytes + (int64_t)j * (4 * Q));
-    const int64_t gi = n * (K / G) + j / (G / 32);
-    const float s = f16_bits_to_f32(scales[gi]);
-    // weight = s*u - s*o, or s*u + m for the minimum layout
-    const float so = META == kMetaMin ? f16_bits_to_f32(static_cast<const uint16_t*>(meta)[gi])
-                   : META == kMetaZp ? -s * (float)static_cast<const uint8_t*>(meta)[gi]
-                                     : -s * (float)(1 << (Q - 1));
-    float w[32];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) w[k] = __builtin_fmaf(s, (float)field<Q>(b.d, k), so);
-#pragma unroll
-    for (int t = 0; t < kF32Tokens; ++t) {
-      if (m0 + t >= M) break;
-      const float* xr = x + (int64_t)(m0 + t) * K + (int64_t)j * 32;
-      float a = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 32; ++k) a = __builtin_fmaf(xr[k], w[k], a);
-      acc[t] += a;
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < kF32Tokens; ++t) {
-    const float v = group_sum<64>(acc[t]);
-    if (lane == 0 && m0 + t < M) y[(int64_t)(m0 + t) * N + n] = v;
-  }
-}
-
 template <int Q, int G, int META, int T = 1>
 hipError_t gemv_dispatch(const uint16_t* x, const uint8_t* codes, const uint16_t* scales,
                          const void* meta, int64_t N, int64_t K, uint16_t* y, hipStream_t stream) {
@@ -706,14 +651,6 @@ hipError_t gemv_dispatch(const uint16_t* x, const uint8_t* codes, const uint16_t
   else
     gemv_kernel<Q, G, META, false, T><<<grid, threads, lds, stream>>>(x, codes, scales, meta, (int)N, (int)K, y,
                                                                       threads);
-  return hipGetLastError();
-}
-
-template <int Q, int G, int META>
-hipError_t f32_dispatch(const float* x, int64_t M, const uint8_t* codes, const uint16_t* scales,
-                        const void* meta, int64_t N, int64_t K, float* y, hipStream_t stream) {
-  const dim3 grid((unsigned)((N + 3) / 4), (unsigned)((M + kF32Tokens - 1) / kF32Tokens));
-  matmul_f32_kernel<Q, G, META><<<grid, 256, 0, stream>>>(x, (int)M, codes, scales, meta, (int)N, (int)K, y);
   return hipGetLastError();
 }
 
@@ -745,12 +682,6 @@ hipError_t launch_gemv2_bf16(const uint16_t* x, const uint8_t* codes, const uint
                              GroupMeta meta, int64_t N, int64_t K, int group, int q, uint16_t* y,
                              hipStream_t stream) {
   SSQ_DISPATCH_QGM(gemv2_dispatch, q, group, meta.kind, x, codes, scales, meta.ptr, N, K, y, stream);
-}
-
-hipError_t launch_matmul_f32(const float* x, int64_t M, const uint8_t* codes,
-                             const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,
-                             int group, int q, float* y, hipStream_t stream) {
-  SSQ_DISPATCH_QGM(f32_dispatch, q, group, meta.kind, x, M, codes, scales, meta.ptr, N, K, y, stream);
 }
 
 }  // namespace ssq

@@ -547,3 +547,19 @@ def test_gemv_two_tokens_full_size(mode):
     w = weights_host(spec)
     x = synth.activations(2, spec.cols, seed=77)
     check_matmul(w, x, 32, 4, mode, rows_idx=sample_rows(spec.rows, 48, seed=mode), tag=f"gemv M=2 full m={mode}")
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 3073, 96),      # past the short-matrix kernel: one super-block of three blocks, ragged rows
+    (3, 1024, 544),     # its largest three-token matrix
+    (4, 17, 32),        # one block: one wavefront, three tokens and a row past the tile's 16
+    (8, 40, 4256),      # 34 super-blocks over 16 wavefronts (three steps for two of them)
+    (9, 33, 2208),      # 16-token stages, 18 super-blocks over 8 wavefronts
+    (35, 50, 1056),     # three token tiles, the last of three
+])
+@pytest.mark.parametrize("q", [2, 3, 4])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_f32_matmul_edges(M, N, K, q, mode):
+    w = rand_w(N, K, seed=M + N + q, bf16=False)
+    x = synth.activations(M, K, seed=M + mode, bf16=False)
+    check_matmul(w, x, 32, q, mode, bf16_w=False, bf16_x=False, tag=f"f32 {M}x{N}x{K}")
