@@ -65,7 +65,8 @@ def kernel_source_sha(files) -> str:
 KERNEL_SOURCES = {
     "gemv": ["gemv.hip", "ssq_internal.h"],
     "gemm": ["gemm.hip", "mfma_dequant.h", "ssq_internal.h"],
-    "batched": ["skinny.hip", "mfma_dequant.h", "ssq_internal.h"],
+    "batched": ["stream.hip", "stream_exact.hip", "stream_q2.hip", "stream_q3.hip", "stream_q4.hip",
+                "stream_kernels.h", "skinny.hip", "mfma_dequant.h", "ssq_internal.h"],
     "quantize": ["quantize.hip", "ssq_internal.h"],
 }
 
@@ -804,8 +805,8 @@ def main() -> int:
         out["roofline_batched"] = {"bound": "hbm", "achieved": round(gbs, 2), "peak": HBM_PEAK_GBS,
                                    "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
                                    "traffic": measured_traffic("batched", args.mode),
-                                   "kernel": ("skinny_stat_kernel" if args.batched_m <= 16 and q in (2, 4) and K % 512 == 0
-                                              else "skinny_split_kernel") + f" (ssq_matmul, M={args.batched_m})",
+                                   "kernel": ("stream_exact_kernel" if args.batched_m <= 16 and q in (2, 4) and K % 512 == 0
+                                              else "stream_kernel") + f" (ssq_matmul, M={args.batched_m})",
                                    "bytes_per_launch": batched_bytes, "avg_launch_us": round(avg * 1e6, 3),
                                    "tflops": round(2 * args.batched_m * N * K / avg / 1e12, 2)}
         out["roofline_batched"]["median_launch_us"], out["roofline_batched"]["cv"] = spread(2, args.layers)

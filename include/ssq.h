@@ -116,12 +116,13 @@ int ssq_quantize_f32(const float* W, int64_t rows, int64_t cols, int group, int 
  *   lives in the scale, so both run the same kernel), o = zp[n, b] otherwise.
  * Products accumulate in fp32; y is rounded to bf16 (half to even).
  * M = 1 and M = 2 run a streaming GEMV (two tokens share each unpacked block);
- * 3 <= M <= 32 (batched decode) shares each weight among the tokens through bf16
- * MFMA: for q = 2 or 4, M <= 16 and K a multiple of 512 (with a workspace, or
- * K <= 2048) the weights enter exactly (the code as 128 + u, the scale and offset
- * applied per 32-weight block in fp32), otherwise each weight is dequantized once
- * and rounded to bf16; larger M runs a tiled kernel that dequantizes weight tiles
- * into LDS and multiplies them with bf16 MFMA.
+ * 3 <= M <= 80 (batched decode, short prompts) streams the weights once and shares
+ * each among the tokens through bf16 MFMA: for q = 2 or 4, M <= 16 and K a multiple
+ * of 512 (with a workspace, or K <= 2048) the weights enter exactly (the code as
+ * 128 + u, the scale and offset applied per 32-weight block in fp32), otherwise each
+ * weight is dequantized once and rounded to bf16; larger M (and large matrices from
+ * M = 33 on) run a tiled kernel that dequantizes weight tiles into LDS and multiplies
+ * them with bf16 MFMA.
  *
  *   x      device, bf16 bits [M, K] row-major, read only
  *   M      >= 0, number of activation rows (tokens)
@@ -144,7 +145,8 @@ int ssq_matmul(const uint16_t* x, int64_t M, const uint8_t* codes, const uint16_
  * blocks of K, so disjoint block ranges can be reduced separately and added).
  * Returns 0 when splitting would not help (M <= 2: the streaming GEMV, or enough
  * output tiles already) or the arguments are invalid.  3 <= M <= 32 sizes the
- * batched-decode kernel's split, larger M the tiled kernel's.
+ * batched-decode kernels' split, larger M the tiled kernel's (which the streaming
+ * kernels use a part of).
  */
 size_t ssq_matmul_workspace_size(int64_t M, int64_t N, int64_t K, int group, int q);
 

@@ -73,15 +73,16 @@ int check_diagnostics(const void* W, int64_t rows, int64_t cols, int group, int 
 ssq::GroupMeta zero_points(const uint8_t* zp) { return {zp, zp ? ssq::kMetaZp : ssq::kMetaNone}; }
 ssq::GroupMeta minimums(const uint16_t* mins) { return {mins, ssq::kMetaMin}; }
 
-// bf16 matmul kernel choice by token count: streaming GEMV (M = 1, 2), skinny-M MFMA
-// kernel (batched decode), tiled MFMA GEMM with an optional split reduction (prefill).
+// bf16 matmul kernel choice by token count: streaming GEMV (M = 1, 2), streaming MFMA
+// kernels (batched decode and short prompts), tiled MFMA GEMM with an optional split
+// reduction (prefill).
 int dispatch_bf16(const uint16_t* x, int64_t M, const uint8_t* codes, const uint16_t* scales,
                   ssq::GroupMeta meta, int64_t N, int64_t K, int group, int q, uint16_t* y,
                   void* workspace, size_t workspace_bytes, hipStream_t stream) {
   if (M == 1) return status_of(ssq::launch_gemv_bf16(x, codes, scales, meta, N, K, group, q, y, stream));
   if (M == 2) return status_of(ssq::launch_gemv2_bf16(x, codes, scales, meta, N, K, group, q, y, stream));
-  if (M <= ssq::kSkinnyMaxM)
-    return status_of(ssq::launch_skinny_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace,
+  if (M <= ssq::kStreamMaxM)
+    return status_of(ssq::launch_stream_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace,
                                              workspace_bytes, stream));
   return status_of(ssq::launch_gemm_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace,
                                          workspace_bytes, stream));
@@ -211,7 +212,7 @@ int ssq_matmul_min(const uint16_t* x, int64_t M, const uint8_t* codes, const uin
 
 size_t ssq_matmul_workspace_size(int64_t M, int64_t N, int64_t K, int group, int q) {
   if (check_matmul_sizes(M, N, K, group, q) != SSQ_OK || M <= 2 || N == 0) return 0;   // GEMV: no split
-  return M <= ssq::kSkinnyMaxM ? ssq::skinny_workspace_bytes(M, N, K, q) : ssq::gemm_workspace_bytes(M, N, K);
+  return M <= ssq::kSkinnyMaxM ? ssq::stream_workspace_bytes(M, N, K, q) : ssq::gemm_workspace_bytes(M, N, K);
 }
 
 int ssq_matmul_ws(const uint16_t* x, int64_t M, const uint8_t* codes, const uint16_t* scales,

@@ -210,14 +210,21 @@ constexpr int64_t kSplitCounterBytes = 65536;
 constexpr int64_t kMaxSplitCounters = kSplitCounterBytes / 4;
 
 
-// Token counts 2..kSkinnyMaxM run the skinny-M kernels (weights dequantized once into
-// MFMA operands; with a workspace the reduction is split across workgroups).
+// Token counts 3..kStreamMaxM run the streaming kernels (stream.hip).  Up to kSkinnyMaxM the
+// workspace size is theirs; above it is the GEMM's, of which they use what they need.
 constexpr int64_t kSkinnyMaxM = 32;
-hipError_t launch_skinny_bf16(const uint16_t* x, int64_t M, const uint8_t* codes,
+constexpr int64_t kStreamMaxM = 80;
+hipError_t launch_stream_bf16(const uint16_t* x, int64_t M, const uint8_t* codes,
                               const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,
                               int group, int q, uint16_t* y, void* workspace, size_t workspace_bytes,
                               hipStream_t stream);
-size_t skinny_workspace_bytes(int64_t M, int64_t N, int64_t K, int q);
+// Batched decode of large matrices with a workspace (skinny.hip; launched from stream.hip).
+hipError_t launch_skinny_bf16(const uint16_t* x, int64_t M, const uint8_t* codes,
+                              const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,
+                              int group, int q, uint16_t* y, void* workspace, bool exact, hipStream_t stream);
+int64_t split_layout_bytes(int64_t M, int64_t N, int64_t K);      // 0: it would not split
+bool stat_layout_bytes(int64_t M, int64_t N, int64_t K, int q, int64_t* bytes);   // whether weights stay exact
+size_t stream_workspace_bytes(int64_t M, int64_t N, int64_t K, int q);
 
 // Sign-rule diagnostics (Sec. 4): per-group margin and gain, optional 3x3 tally.
 hipError_t launch_diagnostics_bf16(const uint16_t* W, int64_t rows, int64_t cols, int group, int q,

@@ -563,3 +563,34 @@ def test_f32_matmul_edges(M, N, K, q, mode):
     w = rand_w(N, K, seed=M + N + q, bf16=False)
     x = synth.activations(M, K, seed=M + mode, bf16=False)
     check_matmul(w, x, 32, q, mode, bf16_w=False, bf16_x=False, tag=f"f32 {M}x{N}x{K}")
+
+
+# ---------------------------------------------------------------------------
+# Streaming kernels (3 <= M <= 80): every tile of tokens (8 to 80) and every number of
+# 16-row tiles per workgroup, sliced and not, and the large matrices that go to the kernels
+# cut across small workgroups instead.
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,workspace", [
+    # exact weights, 8 tokens: 1, 2 (a short last tile), 3 and 4 row tiles a workgroup
+    (5, 17, 512, False), (8, 4100, 1536, False), (5, 9000, 1024, False), (3, 12300, 1024, False),
+    # 16 tokens: 2 to 4 row tiles, four slices of K, one slice
+    (16, 4500, 512, False), (9, 8200, 512, False), (13, 12500, 512, False), (16, 200, 8192, True),
+    (11, 3000, 4608, True),
+    # rounded weights; 9 or 17 blocks of K: a unit of one block after one or two full ones
+    (7, 50, 288, False), (16, 4097, 544, False), (10, 9000, 800, False), (14, 70, 4128, True),
+    (17, 4090, 544, False), (25, 8100, 320, False), (32, 12200, 320, False), (20, 16001, 288, False),
+    (31, 20000, 288, False), (24, 1000, 4128, True),
+    (33, 4000, 288, False), (48, 7000, 288, False), (40, 16000, 288, False), (40, 300, 8192, True),
+    (49, 3000, 288, False), (64, 8100, 544, False), (50, 15000, 288, False), (64, 520, 4128, True),
+    (65, 3001, 288, False), (79, 8000, 288, False), (80, 12000, 1056, False), (66, 16000, 1056, False), (70, 16000, 288, False),
+    (77, 200, 4352, True), (81, 200, 4352, True),
+    # more than 1024 row tiles: exact in one slice, exact in several, rounded
+    (13, 18500, 1024, False), (16, 23000, 6656, True), (24, 18500, 4128, True), (7, 18500, 4128, True),
+])
+@pytest.mark.parametrize("q,mode", [(2, O.SIGNED_SYM), (3, O.ASYM), (4, O.ASYM_MIN), (4, O.SIGNED_SYM)])
+def test_streaming_tiles(M, N, K, workspace, q, mode):
+    w = rand_w(min(N, 997), K, seed=M + N + q)
+    w = np.ascontiguousarray(np.resize(w, (N, K)))          # 997 rows, repeated
+    x = synth.activations(M, K, seed=M + mode)
+    check_matmul(w, x, 32, q, mode, rows_idx=sample_rows(N, n=64, seed=q), tag=f"streaming {M}x{N}x{K} q{q}",
+                 workspace=workspace, repeat=2 if workspace else 1, need_split=False)
