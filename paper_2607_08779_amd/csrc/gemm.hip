@@ -687,6 +687,17 @@ __global__ __launch_bounds__(Cfg<WM>::kThreads) void gemm_kernel(
       }
 }
 
+// Time of the launch, us: 64-deep steps of the busiest workgroup and the partials of the cut
+// tiles (least squares over 44 sizes, W4 g32 signed, 81 to 1024 tokens: 10 % rms; two-bit
+// codes at up to 128 tokens from 27.3 us on 12288x4096 and 26.7 on 28672x2048).
+float gemm_us(const Plan& p, int64_t K, int q, bool split) {
+  const int64_t slots = p.wm == 2 ? 256 : 512, steps = (K / 32 + 1) / 2, cut = split ? p.tiles - p.full : 0;
+  const int64_t whole = (p.tiles - cut + slots - 1) / slots * steps, part = split ? (steps + p.splits - 1) / p.splits : 0;
+  const float partials = (float)(cut * p.splits) / 256.0f;
+  return p.wm == 2 ? 6.0f + 0.953f * (float)(whole + part) + 10.2f * partials
+                   : 4.5f + 0.593f * (float)(whole + part) + (q == 2 ? 8.0f : 13.6f) * partials;
+}
+
 template <int Q, int G, int META>
 hipError_t gemm_dispatch(const uint16_t* x, int64_t M, const uint8_t* codes, const uint16_t* scales,
                          const void* zp, int64_t N, int64_t K, uint16_t* y, void* workspace,
@@ -715,6 +726,17 @@ hipError_t launch_gemm_bf16(const uint16_t* x, int64_t M, const uint8_t* codes,
                             const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,
                             int group, int q, uint16_t* y, void* workspace, size_t workspace_bytes,
                             hipStream_t stream) {
+  // Small tiles (tile.hip) where they are estimated clearly faster, as they measured (W4 g32
+  // signed, us, GEMM / those): 256 tokens on 4096x4096 25.9 / 18.4, 128 on 12288x4096 38.3 /
+  // 28.4, 120 on 28672x2048 35.2 / 34.5; but 200 on 14336x4096 44.5 / 51.4, 235 on 12608x4672
+  // 48.2 / 64.2.  Up to 80 tokens stream.hip has made that choice.
+  if (M > kStreamMaxM) {
+    const Plan p = plan_for(M, N, K);
+    const bool split = p.splits > 1 && workspace != nullptr && (int64_t)workspace_bytes >= p.workspace;
+    const TilePlan t = tile_plan(M, N, K, split ? p.workspace : 0);
+    if (t.us < 0.88f * gemm_us(p, K, q, split))
+      return launch_tile_bf16(t, x, M, codes, scales, meta, N, K, group, q, y, workspace, stream);
+  }
   SSQ_DISPATCH_QGM(gemm_dispatch, q, group, meta.kind, x, M, codes, scales, meta.ptr, N, K, y,
                    workspace, workspace_bytes, stream);
 }

@@ -218,6 +218,16 @@ hipError_t launch_stream_bf16(const uint16_t* x, int64_t M, const uint8_t* codes
                               const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,
                               int group, int q, uint16_t* y, void* workspace, size_t workspace_bytes,
                               hipStream_t stream);
+// Middle token counts (tile.hip): the best small tile, its slices of K (more than one only
+// within `room` bytes of workspace) and its estimated time.
+struct TilePlan {
+  int form, slices;
+  float us;
+};
+TilePlan tile_plan(int64_t M, int64_t N, int64_t K, int64_t room);
+hipError_t launch_tile_bf16(const TilePlan& plan, const uint16_t* x, int64_t M, const uint8_t* codes,
+                            const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K, int group, int q, uint16_t* y,
+                            void* workspace, hipStream_t stream);
 // Batched decode of large matrices with a workspace (skinny.hip; launched from stream.hip).
 hipError_t launch_skinny_bf16(const uint16_t* x, int64_t M, const uint8_t* codes,
                               const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,

@@ -64,12 +64,12 @@ bool rounded_fits(int q, int kind, int tok, int rt) {
 
 struct Cut {
   int rt, slices;
+  float us;
 };
 // `room`: workspace bytes that a sliced launch may use (0: none).
 Cut choose(const Form& f, bool exact, int64_t N, int64_t K, int q, int kind, int64_t room) {
   const int64_t tiles = (N + 15) / 16, units = (K / 32 + 7) / 8;
-  Cut best{1, 1};
-  float best_us = 0.0f;
+  Cut best{1, 1, 0.0f};
   for (int rt = 1; rt <= 5; ++rt) {
     if (f.us[rt - 1] == 0.0f || (!exact && !rounded_fits(q, kind, f.tok, rt))) continue;
     const int64_t rbs = (tiles + rt - 1) / rt;
@@ -83,10 +83,7 @@ Cut choose(const Form& f, bool exact, int64_t N, int64_t K, int q, int kind, int
       const float busy = 0.7f + 0.3f * std::min(1.0f, (float)wgs / kCUs);
       const float us = (float)((wgs + kCUs - 1) / kCUs) * (3.0f + 0.5f * rt + busy * f.us[rt - 1] * (float)((per + 7) / 8)) +
                        (s > 1 ? 1.9f : 0.0f);
-      if (best_us == 0.0f || us < best_us) {
-        best_us = us;
-        best = Cut{rt, s};
-      }
+      if (best.us == 0.0f || us < best.us) best = Cut{rt, s, us};
     }
   }
   return best;
@@ -163,6 +160,14 @@ hipError_t launch_stream_bf16(const uint16_t* x, int64_t M, const uint8_t* codes
   if (tiled_is_faster(M, N, K, q, meta.kind))
     return launch_gemm_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace, workspace_bytes, stream);
   const Cut cut = choose(*form, exact, N, K, q, meta.kind, room);
+  // Above 48 tokens the tiles of tile.hip, where their estimate is clearly lower and the
+  // matrix is not small: 64 tokens on 12288x4096 22.7 here, 20.1 there, 77 tokens on
+  // 4096x12288 26.4 / 24.2, but 52 on 4672x1536 7.4 / 8.1 and 67 on 960x25216 20.1 / 21.5.
+  if (M > 48 && N * K >= 30000000) {
+    const TilePlan plan = tile_plan(M, N, K, room);
+    if (plan.us < 0.9f * cut.us)
+      return launch_tile_bf16(plan, x, M, codes, scales, meta, N, K, group, q, y, workspace, stream);
+  }
   stream::StreamArgs a;
   a.x = x; a.M = M; a.codes = codes; a.scales = scales; a.meta = meta.ptr;
   a.N = N; a.K = K;

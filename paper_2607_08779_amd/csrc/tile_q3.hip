@@ -1,0 +1,10 @@
+// Kernels of the matmul for middle token counts, 3-bit codes.
+#include "tile_kernels.h"
+
+namespace ssq {
+namespace tile {
+
+hipError_t launch_q3(const stream::StreamArgs& a, int kind, int form) { return tile_q<3>(a, kind, form); }
+
+}  // namespace tile
+}  // namespace ssq

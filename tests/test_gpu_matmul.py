@@ -594,3 +594,25 @@ def test_streaming_tiles(M, N, K, workspace, q, mode):
     x = synth.activations(M, K, seed=M + mode)
     check_matmul(w, x, 32, q, mode, rows_idx=sample_rows(N, n=64, seed=q), tag=f"streaming {M}x{N}x{K} q{q}",
                  workspace=workspace, repeat=2 if workspace else 1, need_split=False)
+
+
+# ---------------------------------------------------------------------------
+# Middle token counts: small tiles whose wavefronts split K, 32 x 32 to 128 x 64, unsliced
+# and in slices of K; ragged rows and tokens; units of one block, units without work.
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K,workspace", [
+    (81, 300, 1056, False), (83, 500, 8192, True),              # 32 tokens x 32 rows
+    (100, 40, 288, False), (160, 2050, 2080, False), (120, 500, 16416, True),    # 64 x 32
+    (95, 8100, 1056, False), (190, 600, 4128, True),            # 96 x 32
+    (250, 4000, 1056, False), (200, 900, 12288, True),          # 64 x 64
+    (350, 4070, 2080, False), (147, 2500, 8224, True),          # 96 x 64
+    (300, 4100, 2336, False), (128, 12200, 1056, False),        # 128 x 64
+    (64, 9000, 3424, True),                                     # from the streaming range
+])
+@pytest.mark.parametrize("q,group,mode", [(2, 32, O.ASYM), (3, 32, O.SIGNED_SYM), (4, 32, O.ASYM_MIN), (4, 32, O.SIGNED_SYM)])
+def test_middle_tiles(M, N, K, workspace, q, group, mode):
+    w = rand_w(min(N, 997), K, seed=M + N + q)
+    w = np.ascontiguousarray(np.resize(w, (N, K)))
+    x = synth.activations(M, K, seed=M + mode)
+    check_matmul(w, x, group, q, mode, rows_idx=sample_rows(N, n=64, seed=q), tag=f"middle {M}x{N}x{K} q{q}",
+                 workspace=workspace, repeat=2 if workspace else 1, need_split=False)
