@@ -393,6 +393,18 @@ int q8_tile_for(int64_t M, int64_t N) {
   return best;
 }
 
+}  // namespace
+
+// Time of the launch, us: 3, and the tile's pass over K (10.6 us at K = 4096) per round.
+float q8_gemm_us(int64_t M, int64_t N, int64_t K) {
+  const Q8Tile& t = kQ8Tiles[q8_tile_for(M, N)];
+  const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), slots = t.cost2 ? 512 : 256;
+  const int pass = t.cost2 && tiles > 256 ? t.cost2 : t.cost;
+  return 3.0f + (float)((tiles + slots - 1) / slots) * ((float)pass / 10.0f - 3.0f) * (float)K / 4096.0f;
+}
+
+namespace {
+
 template <int Q, int META>
 hipError_t q8_gemm_dispatch(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes, const uint16_t* scales,
                             const void* meta, int64_t N, int64_t K, int gshift, uint16_t* y, hipStream_t stream) {
