@@ -210,3 +210,21 @@ def test_matmul_q8_tiles(M, N, K, q, mode):
     w = O.bf16_bits_to_f32(synth.weights(spec))
     check_q8_matmul(w, act_bits(M, K, seed=M + mode), 32, q, mode, rows_idx=sample_rows(N, n=40, seed=q),
                     tag=f"tiles {M}x{N}x{K} q={q} m={mode}")
+
+
+# Few tokens: the one-token kernel with a grid row per token on small or long matrices, and
+# the 32x32 tile just past its 16 tokens and on a matrix large enough for the tile at 8.
+@pytest.mark.parametrize("M,N,K", [
+    (2, 5, 32),          # one block, a row past the workgroup's four
+    (3, 1001, 4128),     # 129 blocks: ragged passes over K
+    (16, 130, 8224),     # its most tokens, ragged rows
+    (17, 33, 544),       # 32x32: a ragged tile both ways, two stages, the second one block
+    (8, 8200, 544),      # 32x32: 257 tiles, two workgroups a CU
+])
+@pytest.mark.parametrize("q", [2, 3, 4])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_matmul_q8_few_tokens(M, N, K, q, mode):
+    spec = synth.WeightSpec(N, K, nu=5.0, scale=0.02, outlier_frac=0.001, seed=M + q)
+    w = O.bf16_bits_to_f32(synth.weights(spec))
+    check_q8_matmul(w, act_bits(M, K, seed=M + mode), 32, q, mode, rows_idx=sample_rows(N, n=40, seed=q),
+                    tag=f"few tokens {M}x{N}x{K} q={q} m={mode}")
