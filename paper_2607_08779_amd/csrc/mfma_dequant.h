@@ -22,6 +22,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 __device__ __forceinline__ float f16_lo(uint32_t p) { return (float)__builtin_bit_cast(_Float16, (uint16_t)p); }
 __device__ __forceinline__ float f16_hi(uint32_t p) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(p >> 16)); }
 
+// A constant the compiler does not fold, in a scalar or a vector register: with both,
+// (w & mask) | magic becomes one v_and_or_b32.
+__device__ __forceinline__ uint32_t opaque_s(uint32_t v) { asm("" : "+s"(v)); return v; }
+__device__ __forceinline__ uint32_t opaque_v(uint32_t v) { asm("" : "+v"(v)); return v; }
+
 // Dwords of a block's codes one thread loads: its 1/P share (q=3 loads the whole
 // 12-byte block, whose halves are not dword aligned).
 template <int Q, int P>

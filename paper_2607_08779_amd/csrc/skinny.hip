@@ -366,13 +366,14 @@ __device__ __forceinline__ float scatter_block_sums(float q0, float q1, float q2
 }
 
 // The four bf16 pairs (128 + u) of the 8 codes in `w` (q = 4: 8 nibbles; q = 2: 8
-// fields in the low 16 bits), paired (e0, e4), (e1, e5), (e2, e6), (e3, e7).
+// fields in the low 16 bits), paired (e0, e4), (e1, e5), (e2, e6), (e3, e7).  `mask` and
+// `magic` are opaque, so that each pair is one v_and_or_b32 that the compiler knows: the pairs
+// are an MFMA's B, which and_or() may not write.
 template <int Q>
-__device__ __forceinline__ u32x4 stat_pairs(uint32_t w, uint32_t magic) {
+__device__ __forceinline__ u32x4 stat_pairs(uint32_t w, uint32_t mask, uint32_t magic) {
   if constexpr (Q == 2) w = __builtin_amdgcn_perm(0u, w, 0x0C010C00u);   // bytes {b0, 0, b1, 0}
-  constexpr uint32_t kMask = Q == 4 ? 0x000F000Fu : 0x00030003u;
-  return u32x4{and_or(w, kMask, magic), and_or(w >> Q, kMask, magic), and_or(w >> (2 * Q), kMask, magic),
-               and_or(w >> (3 * Q), kMask, magic)};
+  return u32x4{(w & mask) | magic, ((w >> Q) & mask) | magic, ((w >> (2 * Q)) & mask) | magic,
+               ((w >> (3 * Q)) & mask) | magic};
 }
 
 template <int Q, int G, int META, int MB>
@@ -434,11 +435,10 @@ __device__ __forceinline__ void stat_compute(const uint8_t* stage, const StatRow
                                              int n, int c, f32x4 (&acc)[MB]) {
   using L = StatLayout<Q, G, META, MB>;
   constexpr int KB = L::kBlocks, GB = G / 32;
-  const uint32_t magic = 0x43004300u;
+  const uint32_t mask = opaque_s(Q == 4 ? 0x000F000Fu : 0x00030003u), magic = opaque_v(0x43004300u);
   const uint32_t* const sv = row.s;
   // The block-sum term first: lane (n, c) supplies the coefficient of row n, block
-  // 4i + c, and the fp32 MFMAs start acc from it (C = 0), so no MFMA reads a register
-  // that a VALU instruction has just written.
+  // 4i + c, and the fp32 MFMAs start acc from it (C = 0).
   const int gc = c / GB;
   float coef[KB / 4];
 #pragma unroll
@@ -469,13 +469,8 @@ __device__ __forceinline__ void stat_compute(const uint8_t* stage, const StatRow
     for (int i = 1; i < KB / 4; ++i) acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(XS[i][mb], coef[i], acc[mb], 0, 0, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
-  // Group g's product accumulates in d[g % kRing] and is scaled kLag groups later.  A
-  // VALU read of an MFMA result a few instructions after the MFMA, as the scheduler
-  // places it on its own, was measured to return the register's previous contents (the
-  // wait the compiler inserts is too short here), so every block's MFMA and every
-  // group's scaling sit between scheduling barriers and a result is read three groups
-  // (at least 3 x 12 instructions) after it is written; the last groups, and acc, after
-  // a fixed wait.
+  // Group g's product accumulates in d[g % kRing] and is scaled kLag groups later, so that no
+  // scaling waits for the MFMA it reads.  The fences keep that order.
   constexpr int kLag = 3, kRing = kLag + 1, kG = KB / GB;
   f32x4 d[kRing][MB];
   auto scale_group = [&](int g, const f32x4 (&dg)[MB]) {
@@ -487,7 +482,7 @@ __device__ __forceinline__ void stat_compute(const uint8_t* stage, const StatRow
   };
 #pragma unroll
   for (int j = 0; j < KB; ++j) {
-    const bf16x8 b = __builtin_bit_cast(bf16x8, stat_pairs<Q>(wv[j], magic));
+    const bf16x8 b = __builtin_bit_cast(bf16x8, stat_pairs<Q>(wv[j], mask, magic));
     const int g = j / GB, slot = g % kRing;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
@@ -500,8 +495,6 @@ __device__ __forceinline__ void stat_compute(const uint8_t* stage, const StatRow
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int g = kG > kLag ? kG - kLag : 0; g < kG; ++g) scale_group(g, d[g % kRing]);
 }

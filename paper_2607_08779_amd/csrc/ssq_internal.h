@@ -52,7 +52,10 @@ __device__ __forceinline__ void buffer_block_codes(__amdgpu_buffer_rsrc_t r, uin
 
 // (v & mask) | magic in one v_and_or_b32.  gfx9 VOP3 encodings take no literals and
 // read one SGPR, so the mask rides in an SGPR and the magic in a VGPR; left to itself
-// the compiler emits separate and/or instructions.
+// the compiler emits separate and/or instructions.  Not for the operands of an MFMA: the
+// compiler does not see an asm statement as the vector instruction it is, and leaves out the
+// wait states between it and the MFMA that reads its result (or whose C or D it overwrites).
+// There the mask and the magic are made opaque instead (opaque_s, opaque_v).
 __device__ __forceinline__ uint32_t and_or(uint32_t v, uint32_t mask, uint32_t magic) {
   uint32_t r;
   asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(mask), "v"(magic));

@@ -67,10 +67,6 @@ struct Stream {
   static constexpr int kTileFloats = MB * 256;                     // a row tile's accumulators
 };
 
-// A constant the compiler does not fold, in a scalar or a vector register.
-__device__ __forceinline__ uint32_t opaque_s(uint32_t v) { asm("" : "+s"(v)); return v; }
-__device__ __forceinline__ uint32_t opaque_v(uint32_t v) { asm("" : "+v"(v)); return v; }
-
 // 8 weights s*(u - o) (or s*u + m) in natural order as four bf16 pairs, from 8 codes at bit
 // 0 of `w`.  Each field is OR-ed into the mantissa of fp16 1024 where it lies or one field
 // higher; one fma per weight forms (1024 + u) s + so[0] or (1024 + 2^q u)(s 2^-q) + so[1],
@@ -100,10 +96,8 @@ __device__ __forceinline__ float dequant_offset_hi(float s, uint32_t meta_bits) 
 }
 
 // 8 codes of a block as bf16 pairs 128 + u, paired (e0, e4), (e1, e5), (e2, e6), (e3, e7).
-// `mask` and `magic` are opaque, so that each pair is one v_and_or_b32.  It is not the asm
-// form of and_or: the compiler does not see an asm statement as the vector instruction it
-// is, and leaves out the wait states between it and the MFMA that reads its result (or
-// whose C operand it overwrites).
+// `mask` and `magic` are opaque, so that each pair is one v_and_or_b32 (and_or() may not write
+// an MFMA's operand).
 template <int Q>
 __device__ __forceinline__ bf16x8 code_pairs(uint32_t w, uint32_t mask, uint32_t magic) {
   if constexpr (Q == 2) w = __builtin_amdgcn_perm(0u, w, 0x0C010C00u);   // bytes {b0, 0, b1, 0}

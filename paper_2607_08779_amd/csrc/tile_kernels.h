@@ -38,8 +38,6 @@ namespace tile {
 using stream::kOutOfRange;
 using stream::lds_object;
 using stream::lds_ptr_t;
-using stream::opaque_s;
-using stream::opaque_v;
 using stream::wave_sync;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
