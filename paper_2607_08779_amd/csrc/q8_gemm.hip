@@ -7,26 +7,35 @@
 //
 // What bounds it.  A scale per 32 activations and one per 32 weights: each int32 result
 // of a block (one MFMA is one block deep) needs two vector instructions before it joins
-// the fp32 sum, 32 per lane and 32x32 tile against 13 ns of MFMA, so many tokens are
+// the fp32 sum, 32 per lane and 32x32 tile against 26 ns of MFMA, so many tokens are
 // vector-ALU bound and few tokens latency bound (a stage's loads, LDS round trip and
-// barrier).  The two instructions are t = v s - 1.5*2^23 s (exact product, one rounding)
-// and y += d t: the accumulator starts at the bits of 1.5*2^23, so v read as binary32 is
-// 1.5*2^23 + I exactly and the conversion costs nothing.  A symmetric format's offset
-// joins that start value through one more MFMA (the activations against constant bytes
-// -o), shared by the tile's columns; a zero point is subtracted from the code bytes.
+// barrier).  The two convert I - o R to binary32 (exactly) and add it times d s.  The
+// products d s of a block come from an MFMA of their own, v_mfma_f32_32x32x8_f16 with the
+// scales in one of four k and zeros in the others: exact, so a block term is rounded once,
+// by the fma that adds it, and an infinite scale gives the infinity that it gives in the
+// one-token kernel (q8.hip).  Both halves of the wavefront hold the scale, so the product is
+// 2 d s, and the sum is halved at the end.  Forming t = s (I - o R) first, as
+// s (1.5 * 2^23 + I - o R) - s 1.5 * 2^23, takes no MFMA and the same vector instructions,
+// but makes NaN of an infinite s and rounds t where |I - o R| passes 2^13: 512 tokens on
+// 4096x14336 106.8 us for 110.6, 8 tokens on 4096x12288 27.2 for 25.4.  The minimum layout's
+// d (s I + m R) takes four vector instructions, rounded as in the one-token kernel.  A
+// K-group's sum over up to K / 64 blocks is one chain: at K = 14336 2.5e-4 of the bf16
+// outputs are one step off the correctly rounded one, where 16 shorter chains left 1.6e-4.  A symmetric format's offset joins the start value through one more
+// MFMA (the activations against constant bytes -o), shared by the tile's columns; a zero
+// point is subtracted from the code bytes.
 //
 // Work split.  A workgroup of 8 wavefronts owns a tile of 32 WM tokens x 32 TC outputs and
 // the whole reduction, as 8 / WM K-groups; a wavefront covers 32 tokens and all TC column
-// tiles, so a lane's 16 token scales serve TC tiles.  A stage is SB blocks: the activation
+// tiles.  A stage is SB blocks: the activation
 // codes go straight to LDS, the weight codes through registers, where each block is
-// unpacked once for the whole tile, and the scales beside them as fp32.  The next stage's
+// unpacked once for the whole tile, and the scales beside them.  The next stage's
 // activations and the stage after that's weights are in flight while a stage is
 // multiplied.  With the weights one stage ahead only, a 32x32 tile took 16.1 us at K = 4096
 // (0.95 us a stage, the loads' latency) against 11.2.
 //
 // Measured (W4 g32 signed, graph replays; the kernel this replaces read the weights once
-// per 32 tokens on 16x16x32 MFMA): 512 tokens on 4096x14336 99 us (711 before), on
-// 14336x4096 104 (872); 64 tokens on 4096x4096 11.2 (31), 8 tokens on 12288x4096-like
+// per 32 tokens on 16x16x32 MFMA): 512 tokens on 4096x14336 103 us (711 before), on
+// 14336x4096 109 (872); 64 tokens on 4096x4096 11.2 (31), 8 tokens on 12288x4096-like
 // shapes 15.8 (42), on 4096x4096 10.7 (12.1).
 #include <algorithm>
 #include <type_traits>
@@ -40,19 +49,19 @@ namespace {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 constexpr uint32_t kOutOfRange = 0x80000000u;   // past every buffer's size: loads return 0
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 // The int32 accumulators start at the bits of 1.5 * 2^23, so that an accumulator read as
-// binary32 is 1.5 * 2^23 + I exactly (|I| < 2^17): the conversion is part of the fma
-// that applies the weight scale.
+// binary32 is 1.5 * 2^23 + I exactly (|I| < 2^17) and one subtraction converts it.
 constexpr uint32_t kMagicBits = 0x4B400000u;
 constexpr float kMagic = 12582912.0f;
 
 // SB: 32-k blocks of a stage.
-template <int WM, int TC, int SB>
+template <int META, int WM, int TC, int SB>
 struct Q8Cfg {
   static constexpr int kStageBlocks = SB;
   static constexpr int BM = 32 * WM, BN = 32 * TC;
@@ -60,8 +69,11 @@ struct Q8Cfg {
   static constexpr int NB = kStageBlocks / KG;                 // blocks of a stage per K-group
   static constexpr int kABytes = BM * kStageBlocks * 32;       // activation codes of a stage
   static constexpr int kBBytes = BN * kStageBlocks * 32;       // weight codes, a byte each
-  static constexpr int kDBytes = BM * kStageBlocks * 4;        // token scales, fp32 [block][row]
-  static constexpr int kSBytes = BN * kStageBlocks * 4;        // weight scales, fp32 [block][column]
+  // token scales [block][row]: binary16 for the MFMA that multiplies them with the weights',
+  // binary32 in the minimum layout; weight scales (and minimums) alike [block][column]
+  static constexpr int kScaleSize = META == kMetaMin ? 4 : 2;
+  static constexpr int kDBytes = BM * kStageBlocks * kScaleSize;
+  static constexpr int kSBytes = BN * kStageBlocks * kScaleSize;
   static constexpr int kALoads = kABytes / 1024 / kWaves;      // per wavefront
   static constexpr int kBItems = BN * kStageBlocks;            // weight blocks of a stage
   static constexpr int kBPer = (kBItems + kThreads - 1) / kThreads;
@@ -117,16 +129,22 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
     const int8_t* __restrict__ qx, const uint16_t* __restrict__ dx, int M, const uint8_t* __restrict__ codes,
     const uint16_t* __restrict__ scales, const void* __restrict__ meta, int N, int K, int gshift,
     uint16_t* __restrict__ y) {
-  using C = Q8Cfg<WM, TC, SB>;
+  using C = Q8Cfg<META, WM, TC, SB>;
   constexpr int KG = C::KG, NB = C::NB, BM = C::BM, BN = C::BN, kStageBlocks = SB, kRow = 32 * SB;   // kRow: bytes of a stage row
   constexpr int kMetaSize = META == kMetaZp ? 1 : META == kMetaMin ? 2 : 0;
   constexpr bool MIN = META == kMetaMin;
   uint8_t* const as0 = lds_object<0, C::kABytes>();
   uint8_t* const as1 = lds_object<1, C::kABytes>();
   uint8_t* const bs = lds_object<2, 2 * C::kBBytes>();
-  float* const ds = reinterpret_cast<float*>(lds_object<3, 2 * C::kDBytes>());
-  float* const ss = reinterpret_cast<float*>(lds_object<4, 2 * C::kSBytes>());
-  float* const ms = reinterpret_cast<float*>(lds_object<5, MIN ? 2 * C::kSBytes : 16>());
+  using scale_t = std::conditional_t<MIN, float, uint16_t>;
+  scale_t* const ds = reinterpret_cast<scale_t*>(lds_object<3, 2 * C::kDBytes>());
+  scale_t* const ss = reinterpret_cast<scale_t*>(lds_object<4, 2 * C::kSBytes>());
+  scale_t* const ms = reinterpret_cast<scale_t*>(lds_object<5, MIN ? 2 * C::kSBytes : 16>());
+  auto scale_of = [](uint32_t bits) -> scale_t {
+    if constexpr (MIN) return f16_bits_to_f32(bits);
+    else return (uint16_t)bits;
+  };
+  constexpr int kDCount = C::kDBytes / sizeof(scale_t), kSCount = C::kSBytes / sizeof(scale_t);
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -218,14 +236,14 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
         }
         *reinterpret_cast<u32x4*>(row + (((2 * j + h) ^ (n & 15)) << 4)) = o;
       }
-      ss[buf * (C::kSBytes / 4) + j * BN + n] = f16_bits_to_f32(t.s[i]);
-      if constexpr (MIN) ms[buf * (C::kSBytes / 4) + j * BN + n] = f16_bits_to_f32(t.z[i]);
+      ss[buf * kSCount + j * BN + n] = scale_of(t.s[i]);
+      if constexpr (MIN) ms[buf * kSCount + j * BN + n] = scale_of(t.z[i]);
     }
 #pragma unroll
     for (int i = 0; i < C::kDPer; ++i) {
       const int it = tid + i * kThreads;
       if (C::kDItems % kThreads != 0 && it >= C::kDItems) break;
-      ds[buf * (C::kDBytes / 4) + (it % kStageBlocks) * BM + it / kStageBlocks] = f16_bits_to_f32(t.d[i]);
+      ds[buf * kDCount + (it % kStageBlocks) * BM + it / kStageBlocks] = scale_of(t.d[i]);
     }
   };
 
@@ -235,9 +253,16 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[c][r] = 0.0f;
   const int lr = lane & 31, h = lane >> 5;
-  i32x16 magic;
+  // The int32 accumulators start at 0 and are converted, or (one register read less in the
+  // loop, 16 registers more) at the bits of 1.5 * 2^23, so that read as binary32 they are
+  // 1.5 * 2^23 + I exactly (|I| < 2^17) and one subtraction converts them.  Measured, 512
+  // tokens, us, 0 / 1.5 * 2^23: 128x128 symmetric on 14336x4096 115.7 / 120.0 (spills), zero
+  // point 130.3 / 125.0; the minimum layout 160 / 207 (spills).
+  constexpr bool kZero = MIN || (META == kMetaNone && WM * TC == 16);
+  i32x16 start;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) magic[r] = (int)kMagicBits;
+  for (int r = 0; r < 16; ++r) start[r] = kZero ? 0 : (int)kMagicBits;
+  auto value = [](int v) { return kZero ? (float)v : __int_as_float(v) - kMagic; };
 
   // This K-group's blocks of a stage.
   auto compute = [&](const uint8_t* as, int buf) {
@@ -246,38 +271,46 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
       const int j = grp * NB + k;                      // block of the stage
       const int am = wm * 32 + lr;
       const i32x4 a = act_order<Q>(*reinterpret_cast<const u32x4*>(as + am * kRow + (((2 * j + h) ^ (am & 15)) << 4)));
-      f32x4 dv[4];
+      const scale_t* const dj = ds + buf * kDCount + j * BM + wm * 32;
+      f32x4 dv[4];                                     // minimum layout: the scales of this lane's 16 rows
+      f16x4 da = {};                                   // others: row lr's, as an MFMA operand
+      if constexpr (MIN) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        dv[i] = *reinterpret_cast<const f32x4*>(ds + buf * (C::kDBytes / 4) + j * BM + wm * 32 + 8 * i + 4 * h);
+        for (int i = 0; i < 4; ++i) dv[i] = *reinterpret_cast<const f32x4*>(dj + 8 * i + 4 * h);
+      } else {
+        da[0] = __builtin_bit_cast(_Float16, dj[lr]);
+      }
       i32x16 base;
       if constexpr (META == kMetaNone) {               // magic - o R in every column
         constexpr int kNo = (int)((0x100u - (1u << (Q - 1))) * 0x01010101u);
-        base = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, i32x4{kNo, kNo, kNo, kNo}, magic, 0, 0, 0);
+        base = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, i32x4{kNo, kNo, kNo, kNo}, start, 0, 0, 0);
       } else if constexpr (MIN) {                      // magic + R
-        base = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, i32x4{0x01010101, 0x01010101, 0x01010101, 0x01010101}, magic, 0, 0, 0);
+        base = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, i32x4{0x01010101, 0x01010101, 0x01010101, 0x01010101}, start, 0, 0, 0);
       }
 #pragma unroll
       for (int c = 0; c < TC; ++c) {
         const int bn = c * 32 + lr;
         const i32x4 bv = *reinterpret_cast<const i32x4*>(bs + buf * C::kBBytes + bn * kRow + (((2 * j + h) ^ (bn & 15)) << 4));
-        const float s = ss[buf * (C::kSBytes / 4) + j * BN + bn];
-        const i32x16 v = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, bv, META == kMetaNone ? base : magic, 0, 0, 0);
-        const float off = -kMagic * s;                 // exact: an 11-bit scale times 3 * 2^22
+        const scale_t sn = ss[buf * kSCount + j * BN + bn];
+        const i32x16 v = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, bv, META == kMetaNone ? base : start, 0, 0, 0);
         if constexpr (MIN) {
-          const float m = ms[buf * (C::kSBytes / 4) + j * BN + bn];
-          const float moff = -kMagic * m;
+          const float m = ms[buf * kSCount + j * BN + bn];
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float t = __builtin_fmaf(__int_as_float(v[r]), s, off) + __builtin_fmaf(__int_as_float(base[r]), m, moff);
+            const float t = __builtin_fmaf(sn, value(v[r]), m * value(base[r]));
             acc[c][r] = __builtin_fmaf(dv[r >> 2][r & 3], t, acc[c][r]);
           }
+          // one column tile's results at a time, or the largest tile spills twice as much (167.6 us for 160)
+          if constexpr (WM * TC == 16) __builtin_amdgcn_sched_barrier(0);
         } else {
+          f16x4 sb = {};
+          sb[0] = __builtin_bit_cast(_Float16, sn);
+          f32x16 zero;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float t = __builtin_fmaf(__int_as_float(v[r]), s, off);
-            acc[c][r] = __builtin_fmaf(dv[r >> 2][r & 3], t, acc[c][r]);
-          }
+          for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+          const f32x16 ds2 = __builtin_amdgcn_mfma_f32_32x32x8f16(da, sb, zero, 0, 0, 0);      // 2 d s
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[c][r] = __builtin_fmaf(ds2[r], value(v[r]), acc[c][r]);
         }
       }
     }
@@ -349,14 +382,14 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
     for (int r = 0; r < 16; ++r) {
       const int64_t m = m0 + wm * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
       const int64_t n = n0 + c * 32 + lr;
-      if (m < M && n < N) y[m * N + n] = f32_to_bf16_bits(acc[c][r]);
+      if (m < M && n < N) y[m * N + n] = f32_to_bf16_bits(MIN ? acc[c][r] : 0.5f * acc[c][r]);
     }
 }
 
 template <int Q, int META, int WM, int TC, int SB>
 hipError_t q8_gemm_launch(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes, const uint16_t* scales,
                           const void* meta, int64_t N, int64_t K, int gshift, uint16_t* y, hipStream_t stream) {
-  using C = Q8Cfg<WM, TC, SB>;
+  using C = Q8Cfg<META, WM, TC, SB>;
   const int64_t tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
   q8_gemm_kernel<Q, META, WM, TC, SB><<<dim3((unsigned)tiles), kThreads, 0, stream>>>(
       qx, dx, (int)M, codes, scales, meta, (int)N, (int)K, gshift, y);

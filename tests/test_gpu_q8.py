@@ -228,3 +228,57 @@ def test_matmul_q8_few_tokens(M, N, K, q, mode):
     w = O.bf16_bits_to_f32(synth.weights(spec))
     check_q8_matmul(w, act_bits(M, K, seed=M + mode), 32, q, mode, rows_idx=sample_rows(N, n=40, seed=q),
                     tag=f"few tokens {M}x{N}x{K} q={q} m={mode}")
+
+
+# ---------------------------------------------------------------------------
+# Scales at the ends of binary16: infinities and NaN (a group or block that overflowed) reach
+# the output as they do in the product of the separate terms, on both kernels, and subnormal
+# scales keep their value.
+# ---------------------------------------------------------------------------
+
+def q8_on_gpu(a, r, meta, M, N, K, q, mode):
+    dev = None if meta is None else torch.from_numpy(meta.view(np.int16) if mode == O.ASYM_MIN else meta).cuda()
+    y = ssq.ssq_matmul_q8(torch.from_numpy(a.q).cuda(), torch.from_numpy(a.d.view(np.int16)).cuda(),
+                          torch.from_numpy(r.codes).cuda(), torch.from_numpy(r.scales.view(np.int16)).cuda(), dev,
+                          N, K, 32, q)
+    return y_to_f64(y)
+
+
+@pytest.mark.parametrize("M", [1, 17, 70])        # the one-token kernel, a 32x32 tile, three of them
+@pytest.mark.parametrize("q", [2, 3, 4])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_matmul_q8_infinite_scales(M, q, mode):
+    N, K = 40, 1056
+    rng = np.random.default_rng(q + mode)
+    r = O.quantize(O.bf16_bits_to_f32(bf16_bits(rng.standard_t(5, size=(N, K)) * 0.02)), 32, q, mode)
+    a = O.quantize_act_q8(O.bf16_bits_to_f32(act_bits(M, K, seed=M + q)))
+    r.scales[1, 3], r.scales[2, 32], r.scales[4, 0] = 0x7C00, 0xFC00, 0x7E00       # +inf, -inf, NaN
+    r.scales[6, 5], r.scales[6, 20] = 0x7C00, 0xFC00                               # both signs meet
+    if r.mins is not None:
+        r.mins[8, 7], r.mins[9, 1] = 0x7C00, 0xFC00
+    a.d[M // 2, 4] = 0x7C00
+    with np.errstate(invalid="ignore"):
+        ref = O.matmul_q8(a.q, a.d, r.codes, r.scales, r.zp, N, K, 32, q, mins=r.mins)
+    y = q8_on_gpu(a, r, r.mins if mode == O.ASYM_MIN else r.zp, M, N, K, q, mode)
+    assert np.isinf(ref).any() and np.isnan(ref).any() and (M == 1 or np.isfinite(ref).any())
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    assert np.array_equal(y[np.isinf(ref)], ref[np.isinf(ref)])
+    fine = np.isfinite(ref)
+    if fine.any():
+        assert (np.abs(y[fine] - ref[fine]) <= 2.0 ** -8 * np.abs(ref[fine]) + 1e-5 * np.abs(ref[fine]).max()).all()
+
+
+@pytest.mark.parametrize("M", [1, 17])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_matmul_q8_subnormal_scales(M, mode):
+    N, K, q = 40, 1056, 4
+    rng = np.random.default_rng(mode)
+    r = O.quantize(O.bf16_bits_to_f32(bf16_bits(rng.standard_t(5, size=(N, K)) * 0.02)), 32, q, mode)
+    a = O.quantize_act_q8(O.bf16_bits_to_f32(act_bits(M, K, seed=M)))
+    r.scales[:] = rng.integers(1, 0x400, size=r.scales.shape)
+    a.d[:] = rng.integers(1, 0x400, size=a.d.shape)
+    if r.mins is not None:
+        r.mins[:] = rng.integers(1, 0x400, size=r.mins.shape)
+    ref = O.matmul_q8(a.q, a.d, r.codes, r.scales, r.zp, N, K, 32, q, mins=r.mins)
+    y = q8_on_gpu(a, r, r.mins if mode == O.ASYM_MIN else r.zp, M, N, K, q, mode)
+    assert (np.abs(y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * np.abs(ref).max()).all()
