@@ -30,9 +30,9 @@
 //      sum_k x[m,k] s (u - o) = s * (sum_k x[m,k] (128 + u) - (128 + o) xs[m,b]):
 //    OR-ing a code into the bf16 constant 128 (0x4300 | u == 128 + u) takes one v_and_or
 //    for two weights, the second term is the accumulator's start value, one more MFMA of the
-//    activations against a constant (of every row tile with a zero point: -(128 + z); the
-//    minimum layout starts at -128 xs and adds m xs as -m/128 times that), and one fma per
-//    output and block applies the scale.
+//    activations against a constant (a zero point starts at -128 xs and takes another with -z
+//    for each row tile; the minimum layout starts at -128 xs and adds m xs as -m/128 times
+//    that), and one fma per output and block applies the scale.
 //  * rounded (every other case): a weight is formed as s (u - o) exactly in fp32 and rounded to
 //    bf16 once, so nothing is left to do per output; cheaper from about 32 tokens on.
 #pragma once
@@ -244,13 +244,11 @@ __global__ __launch_bounds__(64 * kWaves) void stream_exact_kernel(
         a[j] = __builtin_bit_cast(bf16x8, u32x4{__builtin_amdgcn_perm(v.z, v.x, kLo), __builtin_amdgcn_perm(v.z, v.x, kHi),
                                                 __builtin_amdgcn_perm(v.w, v.y, kLo), __builtin_amdgcn_perm(v.w, v.y, kHi)});
       }
-      if constexpr (META != kMetaZp) {
-        // -(128 + o) xs[m] (o = 0 for the minimum layout) in every column
-        constexpr uint32_t kOff = META == kMetaMin ? 0xC300C300u : 0xC300C300u | ((1u << (Q - 1)) * 0x00010001u);
-        const bf16x8 off = __builtin_bit_cast(bf16x8, u32x4{kOff, kOff, kOff, kOff});
+      // -(128 + o) xs[m] in every column (o = 0 where a group has a zero point or a minimum)
+      constexpr uint32_t kOff = META != kMetaNone ? 0xC300C300u : 0xC300C300u | ((1u << (Q - 1)) * 0x00010001u);
+      const bf16x8 off = __builtin_bit_cast(bf16x8, u32x4{kOff, kOff, kOff, kOff});
 #pragma unroll
-        for (int j = 0; j < 4; ++j) d0[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], off, zero4, 0, 0, 0);
-      }
+      for (int j = 0; j < 4; ++j) d0[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], off, zero4, 0, 0, 0);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         wave_sync();
@@ -273,9 +271,11 @@ __global__ __launch_bounds__(64 * kWaves) void stream_exact_kernel(
         for (int j = 0; j < 4; ++j) {
           const bf16x8 b = code_pairs<Q>(w[j], mask, magic);
           f32x4 base = d0[j];
-          if constexpr (META == kMetaZp) {
-            const uint32_t zz = 0xC300C300u | __builtin_amdgcn_perm(0u, j < 2 ? zh.x : zh.y, (j & 1) ? 0x03020302u : 0x01000100u);
-            base = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], __builtin_bit_cast(bf16x8, u32x4{zz, zz, zz, zz}), zero4, 0, 0, 0);
+          if constexpr (META == kMetaZp) {       // -z: every byte is exact in bf16, as -(128 + z) is not
+            const uint32_t zp2 = j < 2 ? zh.x : zh.y;
+            const uint32_t zb = __float_as_uint((float)((j & 1) ? (zp2 >> 16) & 0xFFu : zp2 & 0xFFu));
+            const uint32_t zz = 0x80008000u | __builtin_amdgcn_perm(0u, zb, 0x03020302u);
+            base = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], __builtin_bit_cast(bf16x8, u32x4{zz, zz, zz, zz}), base, 0, 0, 0);
           }
           d[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], b, base, 0, 0, 0);
         }

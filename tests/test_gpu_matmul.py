@@ -565,6 +565,31 @@ def test_f32_matmul_edges(M, N, K, q, mode):
     check_matmul(w, x, 32, q, mode, bf16_w=False, bf16_x=False, tag=f"f32 {M}x{N}x{K}")
 
 
+@pytest.mark.parametrize("M,N,K,workspace", [
+    (1, 45, 1536, False), (2, 45, 1536, False),                                    # GEMV
+    (5, 45, 1536, False), (16, 4500, 512, False), (9, 45, 2560, True),             # exact weights
+    (12, 8192, 2048, False),                                                       # exact, large matrix
+    (7, 50, 288, False), (40, 300, 1056, False), (100, 300, 1056, False), (300, 300, 1056, False),
+])
+@pytest.mark.parametrize("q", [2, 4])
+def test_zero_points_past_the_code_range(M, N, K, workspace, q):
+    """Any byte is a zero point (a checkpoint's need not lie on the grid that ssq_quantize
+    makes): odd ones from 129 on, whose 128 + z has nine significant bits."""
+    rng = np.random.default_rng(M + N + q)
+    ref_q = O.quantize(widen(rand_w(min(N, 97), K, seed=M + q), True), 32, q, O.ASYM)
+    ref_q.zp[:] = rng.integers(64, 128, size=ref_q.zp.shape) * 2 + 1
+    rows = np.resize(np.arange(len(ref_q.zp)), N)
+    dev = [torch.from_numpy(np.ascontiguousarray(a[rows])).cuda() for a in (ref_q.codes, ref_q.scales.view(np.int16), ref_q.zp)]
+    x = synth.activations(M, K, seed=M)
+    ws = ssq.ssq_matmul_workspace(M, N, K, 32, q) if workspace else None
+    y = Guarded((M, N), torch.bfloat16)
+    ssq.ssq_matmul(to_device(x, True), *dev, N, K, 32, q, out=y.t, workspace=ws)
+    y.check("zero points past the code range")
+    sel = sample_rows(N, n=64, seed=q)
+    part = ref_q._replace(codes=ref_q.codes[rows[sel]], scales=ref_q.scales[rows[sel]], zp=ref_q.zp[rows[sel]])
+    compare_matmul(y.t, widen(x, True), part, sel, K, 32, q, True, f"zero points {M}x{N}x{K} q{q}", workspace=workspace)
+
+
 # ---------------------------------------------------------------------------
 # Streaming kernels (3 <= M <= 80): every tile of tokens (8 to 80) and every number of
 # 16-row tiles per workgroup, sliced and not, and the large matrices that go to the kernels
