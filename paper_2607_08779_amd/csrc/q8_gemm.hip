@@ -16,16 +16,22 @@
 // one-token kernel (q8.hip).  Both halves of the wavefront hold the scale, so the product is
 // 2 d s, and the sum is halved at the end.  Forming t = s (I - o R) first, as
 // s (1.5 * 2^23 + I - o R) - s 1.5 * 2^23, takes no MFMA and the same vector instructions,
-// but makes NaN of an infinite s and rounds t where |I - o R| passes 2^13: 512 tokens on
-// 4096x14336 106.8 us for 110.6, 8 tokens on 4096x12288 27.2 for 25.4.  The minimum layout's
+// but makes NaN of an infinite s and rounds t where |I - o R| passes 2^13.  The minimum layout's
 // d (s I + m R) takes four vector instructions, rounded as in the one-token kernel.  A
-// K-group's sum over up to K / 64 blocks is one chain: at K = 14336 2.5e-4 of the bf16
-// outputs are one step off the correctly rounded one, where 16 shorter chains left 1.6e-4.  A symmetric format's offset joins the start value through one more
-// MFMA (the activations against constant bytes -o), shared by the tile's columns; a zero
-// point is subtracted from the code bytes.
+// symmetric format's offset joins the start value through one more MFMA (the activations
+// against constant bytes -o), shared by a wavefront's column tiles; a zero point is
+// subtracted from the code bytes.
 //
-// Work split.  A workgroup of 8 wavefronts owns a tile of 32 WM tokens x 32 TC outputs and
-// the whole reduction, as 8 / WM K-groups; a wavefront covers 32 tokens and all TC column
+// Sums: chains of 8 blocks (16 from K = 4640 on), added in turn, then the K-groups as a tree.
+// Their error against 64 bits is that of 16 chains of K / 512 blocks (2-norm of the
+// binary32 sums, K = 4096 / 14336: 8.8e-8 / 1.1e-7 for 8.8e-8 / 1.2e-7); one chain a K-group
+// has 1.4e-7 / 2.5e-7 at two K-groups, and rounds 1.5 times as many outputs to the wrong
+// bf16 neighbour.  The second set of sums leaves registers for two column tiles a wavefront,
+// so the widest tiles have two wavefronts side by side: 512 tokens on 4096x14336 110 us for
+// 102 with single chains and four column tiles, on 14336x4096 120 for 110.
+//
+// Work split.  A workgroup of 8 wavefronts owns a tile of 32 WM tokens x 32 WN TC outputs and
+// the whole reduction, as 8 / (WM WN) K-groups; a wavefront covers 32 tokens and TC column
 // tiles.  A stage is SB blocks: the activation
 // codes go straight to LDS, the weight codes through registers, where each block is
 // unpacked once for the whole tile, and the scales beside them.  The next stage's
@@ -34,9 +40,9 @@
 // (0.95 us a stage, the loads' latency) against 11.2.
 //
 // Measured (W4 g32 signed, graph replays; the kernel this replaces read the weights once
-// per 32 tokens on 16x16x32 MFMA): 512 tokens on 4096x14336 103 us (711 before), on
-// 14336x4096 109 (872); 64 tokens on 4096x4096 11.2 (31), 8 tokens on 12288x4096-like
-// shapes 15.8 (42), on 4096x4096 10.7 (12.1).
+// per 32 tokens on 16x16x32 MFMA): 512 tokens on 4096x14336 110 us (709 before), on
+// 14336x4096 120 (870); 64 tokens on 4096x4096 10.7 (30), 8 tokens on 12288x4096 15.8 (33), on
+// 4096x4096 10.1 (11.8).
 #include <algorithm>
 #include <type_traits>
 
@@ -61,11 +67,11 @@ constexpr uint32_t kMagicBits = 0x4B400000u;
 constexpr float kMagic = 12582912.0f;
 
 // SB: 32-k blocks of a stage.
-template <int META, int WM, int TC, int SB>
+template <int META, int WM, int WN, int TC, int SB>
 struct Q8Cfg {
   static constexpr int kStageBlocks = SB;
-  static constexpr int BM = 32 * WM, BN = 32 * TC;
-  static constexpr int KG = kWaves / WM;                       // K-groups
+  static constexpr int BM = 32 * WM, BN = 32 * TC * WN;
+  static constexpr int KG = kWaves / (WM * WN);                // K-groups
   static constexpr int NB = kStageBlocks / KG;                 // blocks of a stage per K-group
   static constexpr int kABytes = BM * kStageBlocks * 32;       // activation codes of a stage
   static constexpr int kBBytes = BN * kStageBlocks * 32;       // weight codes, a byte each
@@ -124,12 +130,12 @@ __device__ __forceinline__ uint8_t* lds_object() {
   return mem;
 }
 
-template <int Q, int META, int WM, int TC, int SB>
+template <int Q, int META, int WM, int WN, int TC, int SB>
 __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
     const int8_t* __restrict__ qx, const uint16_t* __restrict__ dx, int M, const uint8_t* __restrict__ codes,
     const uint16_t* __restrict__ scales, const void* __restrict__ meta, int N, int K, int gshift,
     uint16_t* __restrict__ y) {
-  using C = Q8Cfg<META, WM, TC, SB>;
+  using C = Q8Cfg<META, WM, WN, TC, SB>;
   constexpr int KG = C::KG, NB = C::NB, BM = C::BM, BN = C::BN, kStageBlocks = SB, kRow = 32 * SB;   // kRow: bytes of a stage row
   constexpr int kMetaSize = META == kMetaZp ? 1 : META == kMetaMin ? 2 : 0;
   constexpr bool MIN = META == kMetaMin;
@@ -148,7 +154,7 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % WM, grp = wave / WM;
+  const int wm = wave % WM, wn = wave / WM % WN, grp = wave / (WM * WN);
   const int tiles_m = (M + BM - 1) / BM;
   int b = (int)blockIdx.x;
   const int tiles = (int)gridDim.x;
@@ -247,30 +253,44 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
     }
   };
 
-  f32x16 acc[TC];
+  f32x16 acc[TC], tot[TC];                             // the chain of the moment, the finished chains
 #pragma unroll
   for (int c = 0; c < TC; ++c)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[c][r] = 0.0f;
+    for (int r = 0; r < 16; ++r) acc[c][r] = tot[c][r] = 0.0f;
+  auto fold = [&]() {
+#pragma unroll
+    for (int c = 0; c < TC; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        tot[c][r] += acc[c][r];
+        acc[c][r] = 0.0f;
+      }
+  };
+  // Stages of a chain (a power of two): 8 blocks, 16 where the number of chains would count
+  // for more.
+  const int chain = std::max(1, (nblk <= 144 ? 8 : 16) / NB);
   const int lr = lane & 31, h = lane >> 5;
-  // The int32 accumulators start at 0 and are converted, or (one register read less in the
-  // loop, 16 registers more) at the bits of 1.5 * 2^23, so that read as binary32 they are
-  // 1.5 * 2^23 + I exactly (|I| < 2^17) and one subtraction converts them.  Measured, 512
-  // tokens, us, 0 / 1.5 * 2^23: 128x128 symmetric on 14336x4096 115.7 / 120.0 (spills), zero
-  // point 130.3 / 125.0; the minimum layout 160 / 207 (spills).
-  constexpr bool kZero = MIN || (META == kMetaNone && WM * TC == 16);
+  // The int32 accumulators start at 0 and are converted, or (16 registers more) at the bits of
+  // 1.5 * 2^23, so that read as binary32 they are 1.5 * 2^23 + I exactly (|I| < 2^17) and one
+  // subtraction converts them: where the registers are free (at the start, 512 tokens on
+  // 14336x4096, zero point, 125 us for 130; the 128x128 symmetric tile and the minimum layout
+  // spill with it).
+  constexpr bool kZero = MIN || (META == kMetaNone && WM * WN == 8);
   i32x16 start;
 #pragma unroll
   for (int r = 0; r < 16; ++r) start[r] = kZero ? 0 : (int)kMagicBits;
   auto value = [](int v) { return kZero ? (float)v : __int_as_float(v) - kMagic; };
 
-  // This K-group's blocks of a stage.
+  // This K-group's blocks of a stage.  A lane's 16-byte piece of block j of any row lies at
+  // row + piece0 ^ 32 j, formed as it is read (kept for every block, the addresses spill).
+  const uint32_t piece0 = (uint32_t)((h ^ (lr & 15)) << 4);
   auto compute = [&](const uint8_t* as, int buf) {
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int j = grp * NB + k;                      // block of the stage
-      const int am = wm * 32 + lr;
-      const i32x4 a = act_order<Q>(*reinterpret_cast<const u32x4*>(as + am * kRow + (((2 * j + h) ^ (am & 15)) << 4)));
+      const uint32_t piece = opaque_v(piece0) ^ (uint32_t)(32 * j);
+      const i32x4 a = act_order<Q>(*reinterpret_cast<const u32x4*>(as + (wm * 32 + lr) * kRow + piece));
       const scale_t* const dj = ds + buf * kDCount + j * BM + wm * 32;
       f32x4 dv[4];                                     // minimum layout: the scales of this lane's 16 rows
       f16x4 da = {};                                   // others: row lr's, as an MFMA operand
@@ -289,8 +309,8 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
       }
 #pragma unroll
       for (int c = 0; c < TC; ++c) {
-        const int bn = c * 32 + lr;
-        const i32x4 bv = *reinterpret_cast<const i32x4*>(bs + buf * C::kBBytes + bn * kRow + (((2 * j + h) ^ (bn & 15)) << 4));
+        const int bn = (wn * TC + c) * 32 + lr;
+        const i32x4 bv = *reinterpret_cast<const i32x4*>(bs + buf * C::kBBytes + bn * kRow + piece);
         const scale_t sn = ss[buf * kSCount + j * BN + bn];
         const i32x16 v = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, bv, META == kMetaNone ? base : start, 0, 0, 0);
         if constexpr (MIN) {
@@ -300,8 +320,6 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
             const float t = __builtin_fmaf(sn, value(v[r]), m * value(base[r]));
             acc[c][r] = __builtin_fmaf(dv[r >> 2][r & 3], t, acc[c][r]);
           }
-          // one column tile's results at a time, or the largest tile spills twice as much (167.6 us for 160)
-          if constexpr (WM * TC == 16) __builtin_amdgcn_sched_barrier(0);
         } else {
           f16x4 sb = {};
           sb[0] = __builtin_bit_cast(_Float16, sn);
@@ -312,6 +330,9 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[c][r] = __builtin_fmaf(ds2[r], value(v[r]), acc[c][r]);
         }
+      }
+      if constexpr (NB > 4) {                          // two blocks at a time: with eight, zero points spill
+        if (k % 2 == 1) __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
@@ -332,6 +353,7 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
     issue_a(s + 1, as_next);
     issue_b(s + 2, freed);
     compute(as, buf);
+    if (((s + 1) & (chain - 1)) == 0) fold();
     __builtin_amdgcn_sched_barrier(0);
     store_b(next, 1 - buf);
     __builtin_amdgcn_sched_barrier(0);
@@ -344,32 +366,32 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
     stage(s + 1, as1, as0, t1, t0, 1);
   }
   if (s < nstages) stage(s, as0, as1, t0, t1, 0);
+  fold();
   wait_vmcnt<0>();
   __syncthreads();
 
   // The K-groups' sums meet pairwise in LDS (group order fixed): group g + half adds into
   // group g until group 0 holds the tile.
   float* const red = reinterpret_cast<float*>(bs);
-  constexpr int kTile = TC * 1024;                     // a wavefront's accumulators
 #pragma unroll
   for (int half = KG / 2; half >= 1; half >>= 1) {
-    // at most half * WM wavefronts write at a time, TC column tiles in turn where LDS is short
+    // at most half * WM * WN = 4 wavefronts write at a time, their TC column tiles in turn
     constexpr int kRoom = 2 * C::kBBytes / 4;
-    const int slot = (grp - half) * WM + wm;
+    const int slot = ((grp - half) * WN + wn) * WM + wm;
 #pragma unroll
     for (int c = 0; c < TC; ++c) {
       if (grp >= half && grp < 2 * half)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
           *reinterpret_cast<f32x4*>(red + slot * 1024 + q4 * 256 + lane * 4) =
-              f32x4{acc[c][4 * q4], acc[c][4 * q4 + 1], acc[c][4 * q4 + 2], acc[c][4 * q4 + 3]};
+              f32x4{tot[c][4 * q4], tot[c][4 * q4 + 1], tot[c][4 * q4 + 2], tot[c][4 * q4 + 3]};
       __syncthreads();
       if (grp < half)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(red + (grp * WM + wm) * 1024 + q4 * 256 + lane * 4);
+          const f32x4 v = *reinterpret_cast<const f32x4*>(red + ((grp * WN + wn) * WM + wm) * 1024 + q4 * 256 + lane * 4);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[c][4 * q4 + e] += v[e];
+          for (int e = 0; e < 4; ++e) tot[c][4 * q4 + e] += v[e];
         }
       __syncthreads();
     }
@@ -381,29 +403,29 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int64_t m = m0 + wm * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-      const int64_t n = n0 + c * 32 + lr;
-      if (m < M && n < N) y[m * N + n] = f32_to_bf16_bits(MIN ? acc[c][r] : 0.5f * acc[c][r]);
+      const int64_t n = n0 + (wn * TC + c) * 32 + lr;
+      if (m < M && n < N) y[m * N + n] = f32_to_bf16_bits(MIN ? tot[c][r] : 0.5f * tot[c][r]);
     }
 }
 
-template <int Q, int META, int WM, int TC, int SB>
+template <int Q, int META, int WM, int WN, int TC, int SB>
 hipError_t q8_gemm_launch(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes, const uint16_t* scales,
                           const void* meta, int64_t N, int64_t K, int gshift, uint16_t* y, hipStream_t stream) {
-  using C = Q8Cfg<META, WM, TC, SB>;
+  using C = Q8Cfg<META, WM, WN, TC, SB>;
   const int64_t tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
-  q8_gemm_kernel<Q, META, WM, TC, SB><<<dim3((unsigned)tiles), kThreads, 0, stream>>>(
+  q8_gemm_kernel<Q, META, WM, WN, TC, SB><<<dim3((unsigned)tiles), kThreads, 0, stream>>>(
       qx, dx, (int)M, codes, scales, meta, (int)N, (int)K, gshift, y);
   return hipGetLastError();
 }
 
 // Tile choice.  Every tile walks all of K, so a launch takes the tile's time for one pass
-// over K times its rounds over the 256 CUs.  Cost of a pass relative to a 32x32 tile's,
-// measured at K = 4096 (10.6 us; 2 workgroups fit a CU, 512 tiles take 16.8): 32x64 15.0,
-// 64x64 19.2, 64x128 31.5, 128x128 52.5.
+// over K times its rounds over the 256 CUs.  Cost of a pass relative to a 32x32 tile's, with
+// the weights in cache.  From memory, 256 tiles at K = 4096, us: 32x32 11.3, 32x64 17.4, 64x64
+// 23.5, 64x128 37.8, 128x128 65.4 (2 workgroups of 32x32 fit a CU).
 struct Q8Tile {
   int bm, bn, cost, cost2;     // cost2: a round of up to 512 tiles where two share a CU, else 0
 };
-constexpr Q8Tile kQ8Tiles[] = {{32, 32, 106, 168}, {32, 64, 150, 0}, {64, 64, 192, 0}, {64, 128, 315, 0}, {128, 128, 525, 0}};
+constexpr Q8Tile kQ8Tiles[] = {{32, 32, 106, 168}, {32, 64, 150, 0}, {64, 64, 192, 0}, {64, 128, 315, 0}, {128, 128, 545, 0}};
 
 int q8_tile_for(int64_t M, int64_t N) {
   int best = 0;
@@ -442,11 +464,11 @@ template <int Q, int META>
 hipError_t q8_gemm_dispatch(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes, const uint16_t* scales,
                             const void* meta, int64_t N, int64_t K, int gshift, uint16_t* y, hipStream_t stream) {
   switch (q8_tile_for(M, N)) {
-    case 0: return q8_gemm_launch<Q, META, 1, 1, 16>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
-    case 1: return q8_gemm_launch<Q, META, 1, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
-    case 2: return q8_gemm_launch<Q, META, 2, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
-    case 3: return q8_gemm_launch<Q, META, 2, 4, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
-    default: return q8_gemm_launch<Q, META, 4, 4, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+    case 0: return q8_gemm_launch<Q, META, 1, 1, 1, 16>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+    case 1: return q8_gemm_launch<Q, META, 1, 1, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+    case 2: return q8_gemm_launch<Q, META, 2, 1, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+    case 3: return q8_gemm_launch<Q, META, 2, 2, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+    default: return q8_gemm_launch<Q, META, 4, 2, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
   }
 }
 

@@ -282,3 +282,33 @@ def test_matmul_q8_subnormal_scales(M, mode):
     ref = O.matmul_q8(a.q, a.d, r.codes, r.scales, r.zp, N, K, 32, q, mins=r.mins)
     y = q8_on_gpu(a, r, r.mins if mode == O.ASYM_MIN else r.zp, M, N, K, q, mode)
     assert (np.abs(y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-5 * np.abs(ref).max()).all()
+
+
+# ---------------------------------------------------------------------------
+# Binary32 sums of the several-token kernel.  A bf16 output goes to the wrong neighbour where
+# the sum's error crosses a midpoint, so the share of such outputs follows the error: a float32
+# model of the sums gives 8.8e-8 (2-norm) for chains of 8 blocks at K = 4096 and 1.4e-7 for one
+# chain in each of two K-groups, 1.1e-7 and 2.5e-7 at K = 14336.  The bars lie between the
+# shares of the two, 7 and 5 standard deviations of the count from them.
+# ---------------------------------------------------------------------------
+
+@pytest.mark.parametrize("M,N,K,share", [
+    (512, 14336, 4096, 1.25e-4),      # 128x128 tiles, one K-group: 1.0e-4 with short chains, 1.5e-4 without
+    (512, 4096, 14336, 1.8e-4),       # 64x128 tiles, two K-groups: 1.2e-4, 2.3e-4
+])
+def test_matmul_q8_sum_error(M, N, K, share):
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    w = 0.02 * torch.randn((N, K), generator=gen, device="cuda")
+    far = torch.rand((N, K), generator=gen, device="cuda") < 1e-3
+    codes, scales, _ = ssq.ssq_quantize(torch.where(far, 20 * w, w).to(torch.bfloat16), 32, 4, O.SIGNED_SYM)
+    qx, dx = ssq.ssq_quantize_act_q8(torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16))
+    y = ssq.ssq_matmul_q8(qx, dx, codes, scales, None, N, K, 32, 4)
+    x64 = (qx.double().view(M, K // 32, 32) * dx.view(torch.float16).double()[..., None]).view(M, K)
+    off = 0
+    for r in range(0, N, 2048):
+        u = torch.stack([codes[r:r + 2048] & 15, codes[r:r + 2048] >> 4], dim=2).double().view(-1, K // 32, 32)
+        w64 = ((u - 8) * scales[r:r + 2048].view(torch.float16).double()[..., None]).view(-1, K)
+        ref = (x64 @ w64.t()).float().to(torch.bfloat16)
+        off += (ref.view(torch.int16) != y[:, r:r + 2048].view(torch.int16)).sum().item()
+    log_metric(test="q8_sum_error", M=M, N=N, K=K, share=off / (M * N))
+    assert off <= share * M * N, f"{off} of {M * N} outputs ({off / (M * N):.2e}) off the correctly rounded value"
