@@ -720,23 +720,34 @@ hipError_t gemm_dispatch(const uint16_t* x, int64_t M, const uint8_t* codes, con
   return hipGetLastError();
 }
 
+// Small tiles (tile.hip) where they are estimated clearly faster, as they measured (W4 g32
+// signed, us, GEMM / those): 256 tokens on 4096x4096 25.9 / 18.4, 128 on 12288x4096 38.3 /
+// 28.4, 120 on 28672x2048 35.2 / 34.5; but 200 on 14336x4096 44.5 / 51.4, 235 on 12608x4672
+// 48.2 / 64.2.  Up to 80 tokens stream.hip has made that choice.
+bool small_tiles(int64_t M, int64_t N, int64_t K, int q, int64_t workspace_bytes, TilePlan* t) {
+  if (M <= kStreamMaxM) return false;
+  const Plan p = plan_for(M, N, K);
+  const bool split = p.splits > 1 && workspace_bytes >= p.workspace;
+  *t = tile_plan(M, N, K, split ? p.workspace : 0);
+  return t->us < 0.88f * gemm_us(p, K, q, split);
+}
+
 }  // namespace
+
+Route gemm_route(int64_t M, int64_t N, int64_t K, int q, int64_t workspace_bytes) {
+  TilePlan t;
+  if (small_tiles(M, N, K, q, workspace_bytes, &t)) return tile_route(t);
+  const Plan p = plan_for(M, N, K);
+  return Route{kRouteGemm, 128 * p.wm, 128, p.splits > 1 && workspace_bytes >= p.workspace ? p.splits : 1};
+}
 
 hipError_t launch_gemm_bf16(const uint16_t* x, int64_t M, const uint8_t* codes,
                             const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,
                             int group, int q, uint16_t* y, void* workspace, size_t workspace_bytes,
                             hipStream_t stream) {
-  // Small tiles (tile.hip) where they are estimated clearly faster, as they measured (W4 g32
-  // signed, us, GEMM / those): 256 tokens on 4096x4096 25.9 / 18.4, 128 on 12288x4096 38.3 /
-  // 28.4, 120 on 28672x2048 35.2 / 34.5; but 200 on 14336x4096 44.5 / 51.4, 235 on 12608x4672
-  // 48.2 / 64.2.  Up to 80 tokens stream.hip has made that choice.
-  if (M > kStreamMaxM) {
-    const Plan p = plan_for(M, N, K);
-    const bool split = p.splits > 1 && workspace != nullptr && (int64_t)workspace_bytes >= p.workspace;
-    const TilePlan t = tile_plan(M, N, K, split ? p.workspace : 0);
-    if (t.us < 0.88f * gemm_us(p, K, q, split))
-      return launch_tile_bf16(t, x, M, codes, scales, meta, N, K, group, q, y, workspace, stream);
-  }
+  TilePlan t;
+  if (small_tiles(M, N, K, q, workspace != nullptr ? (int64_t)workspace_bytes : 0, &t))
+    return launch_tile_bf16(t, x, M, codes, scales, meta, N, K, group, q, y, workspace, stream);
   SSQ_DISPATCH_QGM(gemm_dispatch, q, group, meta.kind, x, M, codes, scales, meta.ptr, N, K, y,
                    workspace, workspace_bytes, stream);
 }

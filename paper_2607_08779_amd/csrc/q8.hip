@@ -275,7 +275,21 @@ hipError_t gemv_q8_dispatch(const int8_t* qx, const uint16_t* dx, int64_t M, con
 // all of K in one workgroup, while that kernel spreads 4 rows over 8 wavefronts.
 constexpr int kGemmMaxK = 32768;
 
+// A few tokens of a small or long matrix: the one-token kernel with a workgroup row per
+// token, which re-reads the weights but walks K with 8 wavefronts per 4 rows.  It takes
+// about 3 us and 7.8 us per 1e8 weights and token (two-bit codes 5.5).  Tiles / one-token,
+// W4, us: 2 tokens on 3333x15872 36.5 / 11.4, 3 on 105x4608 10.9 / 2.6, 3 on 1943x4224 11.6 /
+// 4.9; the tiles keep 8 tokens on 4096x4096, 10.3.
+bool q8_tiles(int64_t M, int64_t N, int64_t K, int q) {
+  const float gemv_us = 3.0f + (float)M * (float)N * (float)K * (q == 2 ? 5.5e-8f : 7.8e-8f);
+  return M > 1 && K <= kGemmMaxK && !(M <= 16 && gemv_us < 0.85f * q8_gemm_us(M, N, K));
+}
+
 }  // namespace
+
+Route q8_route(int64_t M, int64_t N, int64_t K, int q) {
+  return q8_tiles(M, N, K, q) ? q8_gemm_route(M, N) : Route{kRouteQ8Gemv, 1, kRows, 1};
+}
 
 hipError_t launch_quantize_act_q8(const uint16_t* x, int64_t M, int64_t K, int8_t* q, uint16_t* d,
                                   hipStream_t stream) {
@@ -290,13 +304,7 @@ hipError_t launch_quantize_act_q8(const uint16_t* x, int64_t M, int64_t K, int8_
 hipError_t launch_matmul_q8(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes,
                             const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K, int group, int q,
                             uint16_t* y, hipStream_t stream) {
-  // A few tokens of a small or long matrix: the one-token kernel with a workgroup row per
-  // token, which re-reads the weights but walks K with 8 wavefronts per 4 rows.  It takes
-  // about 3 us and 7.8 us per 1e8 weights and token (two-bit codes 5.5).  Tiles / one-token,
-  // W4, us: 2 tokens on 3333x15872 36.5 / 11.4, 3 on 105x4608 10.9 / 2.6, 3 on 1943x4224 11.6 /
-  // 4.9; the tiles keep 8 tokens on 4096x4096, 10.3.
-  const float gemv_us = 3.0f + (float)M * (float)N * (float)K * (q == 2 ? 5.5e-8f : 7.8e-8f);
-  if (M > 1 && K <= kGemmMaxK && !(M <= 16 && gemv_us < 0.85f * q8_gemm_us(M, N, K)))
+  if (q8_tiles(M, N, K, q))
     return launch_q8_gemm(qx, dx, M, codes, scales, meta, N, K, group, q, y, stream);
   SSQ_DISPATCH_QGM(gemv_q8_dispatch, q, group, meta.kind, qx, dx, M, codes, scales, meta.ptr, N, K, y, stream);
 }

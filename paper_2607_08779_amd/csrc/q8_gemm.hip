@@ -450,6 +450,11 @@ int q8_tile_for(int64_t M, int64_t N) {
 
 }  // namespace
 
+Route q8_gemm_route(int64_t M, int64_t N) {
+  const Q8Tile& t = kQ8Tiles[q8_tile_for(M, N)];
+  return Route{kRouteQ8Tile, t.bm, t.bn, 1};
+}
+
 // Time of the launch, us: 3, and the tile's pass over K (10.6 us at K = 4096) per round.
 float q8_gemm_us(int64_t M, int64_t N, int64_t K) {
   const Q8Tile& t = kQ8Tiles[q8_tile_for(M, N)];

@@ -705,6 +705,15 @@ hipError_t launch_skinny_bf16(const uint16_t* x, int64_t M, const uint8_t* codes
                    stream);
 }
 
+Route skinny_route(int64_t M, int64_t N, int64_t K, int q, bool exact) {
+  if (exact) {
+    const StatPlan p = stat_plan(M, N, K, q);
+    return Route{kRouteStat, 16, p.tiles_per_run, p.slices};
+  }
+  const SplitPlan p = split_plan(M, N, K);
+  return Route{kRouteSplit, 16 * p.mb, kSplitRows, p.splits};
+}
+
 int64_t split_layout_bytes(int64_t M, int64_t N, int64_t K) { return split_plan(M, N, K).workspace; }
 
 bool stat_layout_bytes(int64_t M, int64_t N, int64_t K, int q, int64_t* bytes) {

@@ -252,6 +252,21 @@ int ssq_matmul_min_ws(const uint16_t* x, int64_t M, const uint8_t* codes, const 
                        stream);
 }
 
+// Which kernel a matmul runs (a Route), for tests: a retuned rule must not move one to another
+// kernel unnoticed.  Not part of the boundary; nothing is launched.  kind: metadata layout,
+// aligned: scales and metadata at 16-byte addresses.
+int ssq_internal_route(int64_t M, int64_t N, int64_t K, int group, int q, int kind, int aligned,
+                       size_t workspace_bytes, int q8, int out[4]) {
+  if (check_matmul_sizes(M, N, K, group, q) != SSQ_OK || M == 0 || N == 0 || kind < 0 || kind > 2) return SSQ_EINVAL;
+  const int64_t have = (int64_t)workspace_bytes;
+  const ssq::Route r = q8 ? ssq::q8_route(M, N, K, q)
+                     : M <= 2 ? ssq::Route{ssq::kRouteGemv, (int)M, 0, 1}
+                     : M <= ssq::kStreamMaxM ? ssq::stream_route(M, N, K, q, kind, aligned != 0, have)
+                                             : ssq::gemm_route(M, N, K, q, have);
+  out[0] = r.kernel; out[1] = r.tokens; out[2] = r.rows; out[3] = r.slices;
+  return SSQ_OK;
+}
+
 int ssq_matmul_f32(const float* x, int64_t M, const uint8_t* codes, const uint16_t* scales,
                    const uint8_t* zp, int64_t N, int64_t K, int group, int q, float* y,
                    hipStream_t stream) {

@@ -221,6 +221,18 @@ hipError_t launch_stream_bf16(const uint16_t* x, int64_t M, const uint8_t* codes
                               const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K,
                               int group, int q, uint16_t* y, void* workspace, size_t workspace_bytes,
                               hipStream_t stream);
+// The kernel that a bf16 or Q8_0 matmul runs and how it cuts the product, as the launchers
+// choose them: tokens and weight rows of a workgroup (row tiles of a run for kStat, 0 where
+// there is one form only) and slices of K.  Reported to tests through ssq_internal_route.
+enum RouteKernel : int { kRouteGemv = 0, kRouteExact, kRouteRounded, kRouteStat, kRouteSplit, kRouteTile, kRouteGemm, kRouteQ8Gemv, kRouteQ8Tile };
+struct Route {
+  int kernel, tokens, rows, slices;
+};
+Route stream_route(int64_t M, int64_t N, int64_t K, int q, int kind, bool aligned, int64_t workspace_bytes);
+Route skinny_route(int64_t M, int64_t N, int64_t K, int q, bool exact);
+Route gemm_route(int64_t M, int64_t N, int64_t K, int q, int64_t workspace_bytes);
+Route q8_route(int64_t M, int64_t N, int64_t K, int q);
+Route q8_gemm_route(int64_t M, int64_t N);
 // Middle token counts (tile.hip): the best small tile, its slices of K (more than one only
 // within `room` bytes of workspace) and its estimated time.
 struct TilePlan {
@@ -228,6 +240,7 @@ struct TilePlan {
   float us;
 };
 TilePlan tile_plan(int64_t M, int64_t N, int64_t K, int64_t room);
+Route tile_route(const TilePlan& plan);
 hipError_t launch_tile_bf16(const TilePlan& plan, const uint16_t* x, int64_t M, const uint8_t* codes,
                             const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K, int group, int q, uint16_t* y,
                             void* workspace, hipStream_t stream);

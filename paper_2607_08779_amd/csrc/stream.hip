@@ -138,50 +138,87 @@ bool tiled_is_faster(int64_t M, int64_t N, int64_t K, int q, int kind) {
   return q == 4 && (K < 1024 || (weights >= 190000000 && !rounded_fits(q, kind, 80, 4)));
 }
 
+// What runs and its cut.  `have`: workspace bytes (0: none), `aligned`: scales and metadata at
+// 16-byte addresses.
+struct Choice {
+  int kernel;           // kRouteGemm: launch_gemm_bf16
+  bool exact;
+  int tok;
+  Cut cut;
+  TilePlan tile;
+};
+Choice choose_kernel(int64_t M, int64_t N, int64_t K, int q, int kind, bool aligned, int64_t have) {
+  // Exact weights: the sizes that allow it, rows of scales and metadata that start 16-byte
+  // aligned, and the workspace its layout names (or a K that needs none).
+  int64_t exact_bytes = 0;
+  Choice c{};
+  c.exact = stat_layout_bytes(M, N, K, q, &exact_bytes) && aligned && have >= exact_bytes;
+  const Form* form = c.exact ? (M <= 8 ? &kExactForms[0] : &kExactForms[1]) : &kRoundedForms[0];
+  if (!c.exact)
+    while (form->tok < M) ++form;
+  c.tok = form->tok;
+  const int64_t named = c.exact ? exact_bytes : M <= kSkinnyMaxM ? split_layout_bytes(M, N, K) : (int64_t)gemm_workspace_bytes(M, N, K);
+  const int64_t room = named > 0 && have >= named ? named : 0;
+  c.kernel = c.exact ? kRouteExact : kRouteRounded;
+  if (blocked_is_faster(M, N, K, q, kind, c.exact, room > 0)) {
+    c.kernel = c.exact ? kRouteStat : kRouteSplit;
+    return c;
+  }
+  if (tiled_is_faster(M, N, K, q, kind)) {
+    c.kernel = kRouteGemm;
+    return c;
+  }
+  c.cut = choose(*form, c.exact, N, K, q, kind, room);
+  // Above 48 tokens the tiles of tile.hip, where their estimate is clearly lower and the
+  // matrix is not small: 64 tokens on 12288x4096 22.7 here, 20.1 there, 77 tokens on
+  // 4096x12288 26.4 / 24.2, but 52 on 4672x1536 7.4 / 8.1 and 67 on 960x25216 20.1 / 21.5.
+  if (M > 48 && N * K >= 30000000) {
+    c.tile = tile_plan(M, N, K, room);
+    if (c.tile.us < 0.9f * c.cut.us) c.kernel = kRouteTile;
+  }
+  return c;
+}
+
 }  // namespace
+
+Route stream_route(int64_t M, int64_t N, int64_t K, int q, int kind, bool aligned, int64_t workspace_bytes) {
+  const Choice c = choose_kernel(M, N, K, q, kind, aligned, workspace_bytes);
+  switch (c.kernel) {
+    case kRouteStat: case kRouteSplit: return skinny_route(M, N, K, q, c.exact);
+    case kRouteGemm: return gemm_route(M, N, K, q, workspace_bytes);
+    case kRouteTile: return tile_route(c.tile);
+    default: return Route{c.kernel, c.tok, 16 * c.cut.rt, c.cut.slices};
+  }
+}
 
 hipError_t launch_stream_bf16(const uint16_t* x, int64_t M, const uint8_t* codes, const uint16_t* scales, GroupMeta meta,
                               int64_t N, int64_t K, int group, int q, uint16_t* y, void* workspace,
                               size_t workspace_bytes, hipStream_t stream) {
   if (M < 3 || M > kStreamMaxM) return hipErrorInvalidValue;
-  const int64_t have = workspace != nullptr ? (int64_t)workspace_bytes : 0;
-  // Exact weights: the sizes that allow it, rows of scales and metadata that start 16-byte
-  // aligned, and the workspace its layout names (or a K that needs none).
-  int64_t exact_bytes = 0;
-  const bool exact = stat_layout_bytes(M, N, K, q, &exact_bytes) && reinterpret_cast<uintptr_t>(scales) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(meta.ptr) % 16 == 0 && have >= exact_bytes;
-  const Form* form = exact ? (M <= 8 ? &kExactForms[0] : &kExactForms[1]) : &kRoundedForms[0];
-  if (!exact)
-    while (form->tok < M) ++form;
-  const int64_t named = exact ? exact_bytes : M <= kSkinnyMaxM ? split_layout_bytes(M, N, K) : (int64_t)gemm_workspace_bytes(M, N, K);
-  const int64_t room = named > 0 && have >= named ? named : 0;
-  if (blocked_is_faster(M, N, K, q, meta.kind, exact, room > 0))
-    return launch_skinny_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace, exact, stream);
-  if (tiled_is_faster(M, N, K, q, meta.kind))
-    return launch_gemm_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace, workspace_bytes, stream);
-  const Cut cut = choose(*form, exact, N, K, q, meta.kind, room);
-  // Above 48 tokens the tiles of tile.hip, where their estimate is clearly lower and the
-  // matrix is not small: 64 tokens on 12288x4096 22.7 here, 20.1 there, 77 tokens on
-  // 4096x12288 26.4 / 24.2, but 52 on 4672x1536 7.4 / 8.1 and 67 on 960x25216 20.1 / 21.5.
-  if (M > 48 && N * K >= 30000000) {
-    const TilePlan plan = tile_plan(M, N, K, room);
-    if (plan.us < 0.9f * cut.us)
-      return launch_tile_bf16(plan, x, M, codes, scales, meta, N, K, group, q, y, workspace, stream);
+  const bool aligned = reinterpret_cast<uintptr_t>(scales) % 16 == 0 && reinterpret_cast<uintptr_t>(meta.ptr) % 16 == 0;
+  const Choice c = choose_kernel(M, N, K, q, meta.kind, aligned, workspace != nullptr ? (int64_t)workspace_bytes : 0);
+  switch (c.kernel) {
+    case kRouteStat: case kRouteSplit:
+      return launch_skinny_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace, c.exact, stream);
+    case kRouteGemm:
+      return launch_gemm_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace, workspace_bytes, stream);
+    case kRouteTile:
+      return launch_tile_bf16(c.tile, x, M, codes, scales, meta, N, K, group, q, y, workspace, stream);
   }
   stream::StreamArgs a;
   a.x = x; a.M = M; a.codes = codes; a.scales = scales; a.meta = meta.ptr;
   a.N = N; a.K = K;
   a.gshift = group == 32 ? 0 : group == 64 ? 1 : 2;
-  a.slices = cut.slices;
+  a.slices = c.cut.slices;
   a.y = y;
-  a.partials = cut.slices > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + kSplitCounterBytes) : nullptr;
+  a.partials = c.cut.slices > 1 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + kSplitCounterBytes) : nullptr;
   a.counters = static_cast<unsigned int*>(workspace);
   a.stream = stream;
-  if (exact) return stream::launch_exact(a, q, meta.kind, form->tok, cut.rt);
+  if (c.exact) return stream::launch_exact(a, q, meta.kind, c.tok, c.cut.rt);
   switch (q) {
-    case 2: return stream::launch_rounded_q2(a, meta.kind, form->tok, cut.rt);
-    case 3: return stream::launch_rounded_q3(a, meta.kind, form->tok, cut.rt);
-    default: return stream::launch_rounded_q4(a, meta.kind, form->tok, cut.rt);
+    case 2: return stream::launch_rounded_q2(a, meta.kind, c.tok, c.cut.rt);
+    case 3: return stream::launch_rounded_q3(a, meta.kind, c.tok, c.cut.rt);
+    default: return stream::launch_rounded_q4(a, meta.kind, c.tok, c.cut.rt);
   }
 }
 

@@ -52,6 +52,10 @@ TilePlan tile_plan(int64_t M, int64_t N, int64_t K, int64_t room) {
   return best;
 }
 
+Route tile_route(const TilePlan& plan) {
+  return Route{kRouteTile, kForms[plan.form].bm, kForms[plan.form].bn, plan.slices};
+}
+
 hipError_t launch_tile_bf16(const TilePlan& plan, const uint16_t* x, int64_t M, const uint8_t* codes,
                             const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K, int group, int q, uint16_t* y,
                             void* workspace, hipStream_t stream) {

@@ -1,13 +1,14 @@
 """GPU parity at the boundary's largest reduction length (K = 2^22, the ABI limit set by
-32-bit buffer offsets), through every kernel family: quantize, GEMV, batched decode with
-its split reduction, the prefill GEMM with its split reduction, Q8_0 and the sign-rule
-diagnostics.  Few rows, so the oracle stays cheap."""
+32-bit buffer offsets): quantize, GEMV, the streaming kernels with exact and rounded weights
+in slices of K, Q8_0 and the sign-rule diagnostics.  Few rows, so the oracle stays cheap (the
+GEMM and the kernels of large matrices need more rows than a test can hold at this K)."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import ssq_oracle as O
 from paper_2607_08779_amd import ssq, synth
+from tests.routes import route
 from tests.parity_common import assert_within, log_metric, matmul_error_bound, rel_l2, to_device, y_to_f64
 
 pytestmark = pytest.mark.gpu
@@ -66,9 +67,10 @@ def test_gemv_and_q8_at_max_k():
 
 @pytest.mark.parametrize("M", [16, 40])
 def test_split_kernels_at_max_k(M):
-    """M = 16: batched decode; M = 40: the GEMM; both with the split reduction (the
-    largest slice counts) and a ragged weight row block."""
+    """Streaming kernels in eight slices of K (M = 16: exact weights, M = 40: rounded), with a
+    ragged row tile."""
     N = 20
+    assert route(M, N, KMAX, 32, 4, O.SIGNED_SYM, True) == ("exact" if M == 16 else "rounded", 16 if M == 16 else 48, 16, 8)
     wb = weights(N, KMAX, seed=M)
     dev, r = quantized(wb, 32, 4)
     x = synth.activations(M, KMAX, seed=M + 1)
@@ -90,9 +92,9 @@ def test_diagnostics_at_max_k():
 
 
 def test_large_row_count():
-    """Two million and three weight rows (K = 64): grids of 2^19 GEMV workgroups and 2^14
-    batched-decode and GEMM row blocks, ragged at the end.  Quantize, the GEMV at M = 1
-    and 2, batched decode (M = 16) and the GEMM (M = 40) with their workspaces, and the
+    """Two million and three weight rows (K = 64): grids of 2^19 GEMV workgroups, 2^15 streaming
+    workgroups and 2^14 GEMM row blocks, ragged at the end.  Quantize, the GEMV at M = 1
+    and 2, batched decode (M = 16, 40) and the GEMM (M = 96) with their workspaces, and the
     sign-rule diagnostics, each against the oracle on sampled rows (the last ones
     included); the tally against the counts of the full outputs."""
     N, K, group, q = (1 << 21) + 3, 64, 32, 4
@@ -106,7 +108,8 @@ def test_large_row_count():
     r = O.quantize(wf, group, q, O.SIGNED_SYM)
     assert np.array_equal(codes.cpu().numpy()[rows], r.codes)
     assert np.array_equal(scales.cpu().numpy().view(np.uint16)[rows], r.scales)
-    for M in (1, 2, 16, 40):
+    assert route(96, N, K, group, q, O.SIGNED_SYM, True).kernel == "gemm"
+    for M in (1, 2, 16, 40, 96):
         x = synth.activations(M, K, seed=M)
         ws = ssq.ssq_matmul_workspace(M, N, K, group, q)
         y = ssq.ssq_matmul(to_device(x, True), codes, scales, zp, N, K, group, q, workspace=ws)

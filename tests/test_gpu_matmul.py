@@ -1,5 +1,7 @@
-"""GPU parity: ssq_matmul (GEMV at M = 1, 2, skinny-M MFMA kernel at 3 <= M <= 32, tiled
-MFMA GEMM above) and ssq_matmul_f32 against the binary64 CPU oracle.
+"""GPU parity: ssq_matmul (GEMV at M = 1, 2, streaming MFMA kernels at 3 <= M <= 80 and the
+kernels of large matrices at 3 <= M <= 32, small tiles and the GEMM above) and
+ssq_matmul_f32 against the binary64 CPU oracle.  Where a test is about one kernel it asserts
+the library's choice (tests/routes.py).
 
 Every comparison is element-wise (tests/parity_common.py states the bound and its
 derivation): one bf16 rounding of the output plus binary32 accumulation slack, plus,
@@ -16,6 +18,7 @@ import torch
 
 from oracle import ssq_oracle as O
 from paper_2607_08779_amd import ssq, synth
+from tests.routes import route
 from tests.parity_common import (Guarded, assert_quant_equal, assert_within, bf16_round_f64,
                                  guarded_quant_outputs, log_metric, matmul_error_bound, rel_l2,
                                  sample_rows, to_device, weights_host, widen, y_to_f64)
@@ -38,11 +41,9 @@ def quantize_guarded(W, rows, cols, group, q, mode, tag=""):
 
 
 def exact_weight_path(M, K, q, workspace):
-    """Whether ssq_matmul runs the activation-stationary batched-decode kernel: q = 2 or
-    4, 3 <= M <= 16, K a multiple of a wavefront's range of 512 weights and either a
-    workspace or at most four ranges (one slice of K).  It keeps every weight exact,
-    where the dequantizing MFMA kernels round s (u - o) to bf16, so it is held to the
-    exact-weight bound."""
+    """Whether ssq_matmul runs a batched-decode kernel that keeps every weight exact: q = 2 or
+    4, 3 <= M <= 16, K a multiple of 512 and either a workspace or K <= 2048.  The other
+    MFMA kernels round s (u - o) to bf16, so these are held to the exact-weight bound."""
     if q not in (2, 4) or not 3 <= M <= 16:
         return False
     return K % 512 == 0 and (workspace or K <= 2048)
@@ -53,7 +54,7 @@ def compare_matmul(y, x_real, ref_q, sel, K, group, q, bf16_x, tag, workspace=Fa
     M = x_real.shape[0]
     y_ref = O.matmul(x_real, ref_q.codes, ref_q.scales, ref_q.zp, len(sel), K, group, q, mins=ref_q.mins)
     w_hat = O.dequantize(ref_q.codes, ref_q.scales, ref_q.zp, K, group, q, ref_q.mins)
-    # batched decode and prefill round W_hat to bf16, except the activation-stationary kernel
+    # batched decode and prefill round W_hat to bf16, except the exact-weight kernels
     rounded = bf16_x and M > 2 and not exact_weight_path(M, K, q, workspace)
     bound, S = matmul_error_bound(x_real, w_hat, y_ref, rounded, f32=not bf16_x)
     y_all = y_to_f64(y)
@@ -169,7 +170,7 @@ def test_gemv_unaligned_metadata(mode):
 @pytest.mark.parametrize("M", [16, 96, 300])
 @pytest.mark.parametrize("mode", MODES)
 def test_matmul_unaligned_metadata(M, mode):
-    """Batched decode and the GEMM with scales (and zero points or minimums) that start
+    """Batched decode and small tiles with scales (and zero points or minimums) that start
     off a 4-byte boundary (offsets of one element): the result equals the aligned call
     bit for bit, with and without the split workspace."""
     N, K = 200, 1056
@@ -196,69 +197,109 @@ def test_matmul_unaligned_metadata(M, mode):
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("group", [32, 128])
 @pytest.mark.parametrize("mode", MODES)
-def test_gemm_ragged_all_formats(q, group, mode):
-    # M=200, N=300 leave partial 128x128 tiles in both directions; at g=32, K=1056 is an odd
-    # number of 32-blocks (half of the last 64-deep step is empty)
+def test_tile_ragged_all_formats(q, group, mode):
+    # small tiles: M=200, N=300 leave partial 32x32 tiles in both directions; at g=32, K=1056
+    # is an odd number of 32-blocks (half of the last 64-deep step is empty)
     K = 1056 if group == 32 else 1152
+    assert route(200, 300, K, group, q, mode).kernel == "tile"
     w = rand_w(300, K, seed=7 * q + group)
     x = synth.activations(200, K, seed=q + group)
-    check_matmul(w, x, group, q, mode, tag=f"gemm 200x300x{K}")
+    check_matmul(w, x, group, q, mode, tag=f"tile 200x300x{K}")
 
 
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("group", [32, 64, 128])
 @pytest.mark.parametrize("mode", MODES)
-def test_skinny_all_formats(q, group, mode):
-    # batched decode (2 <= M <= 32): N=45 leaves a partial 16-row workgroup; K is an odd
-    # number of 32-blocks at g=32 and g=64, so the last 128-wide super-block is partial
+def test_rounded_all_formats(q, group, mode):
+    # streaming, rounded weights: N=45 leaves a partial 16-row tile; K leaves a partial unit of
+    # 256 (one, two or four blocks)
     K = {32: 1056, 64: 1088, 128: 1152}[group]
+    assert route(7, 45, K, group, q, mode).kernel == "rounded"
     w = rand_w(45, K, seed=3 * q + group + mode)
     x = synth.activations(7, K, seed=q * group)
-    check_matmul(w, x, group, q, mode, tag=f"skinny 7x45x{K}")
+    check_matmul(w, x, group, q, mode, tag=f"rounded 7x45x{K}")
 
 
 @pytest.mark.parametrize("M", [2, 15, 16, 17, 31, 32])
-def test_skinny_token_counts(M):
-    # one and two 16-token MFMA blocks, both partial and full; K=14336 spreads 112
-    # super-blocks over 16 wavefronts
+def test_rounded_token_counts(M):
+    # one and two 16-token MFMA blocks, both partial and full (no workspace: weights rounded;
+    # M=2 the GEMV); K=14336 spreads 56 units over 8 wavefronts
+    assert M == 2 or route(M, 40, 14336, 32, 4, O.ASYM).kernel == "rounded"
     w = rand_w(40, 14336, seed=M)
     x = synth.activations(M, 14336, seed=M)
     for mode in MODES:
-        check_matmul(w, x, 32, 4, mode, tag=f"skinny M={M}")
+        check_matmul(w, x, 32, 4, mode, tag=f"rounded M={M}")
 
 
 @pytest.mark.parametrize("K", [32, 64, 128, 4096 + 96])
-def test_skinny_short_and_odd_reductions(K):
-    # fewer super-blocks than wavefronts, a lone partial super-block, a partial last one
+def test_rounded_short_and_odd_reductions(K):
+    # a lone partial unit, a partial last one
     w = rand_w(33, K, seed=K + 1)
     x = synth.activations(16, K, seed=K + 1)
     for mode in MODES:
-        check_matmul(w, x, 32, 3, mode, tag=f"skinny K={K}")
+        check_matmul(w, x, 32, 3, mode, tag=f"rounded K={K}")
 
 
 @pytest.mark.parametrize("K", [32, 64, 96, 128, 192])
 @pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM])
-def test_gemm_short_reductions(K, mode):
-    # one or two 64-deep windows per tile: the loads of the window after the last one
-    # (issued at the start of the tile, or by the last window) lie past K and read
-    # nothing the result uses; signed scales take the two-window start, zero points not
+def test_tile_short_reductions(K, mode):
+    # small tiles of one unit, not full: most wavefronts have no work
+    assert route(200, 300, K, 32, 4, mode).kernel == "tile"
     w = rand_w(300, K, seed=K + mode)
     x = synth.activations(200, K, seed=K)
-    check_matmul(w, x, 32, 4, mode, tag=f"gemm 200x300x{K}")
+    check_matmul(w, x, 32, 4, mode, tag=f"tile 200x300x{K}")
+
+
+@pytest.mark.parametrize("M,N", [(300, 5000), (120, 6000)])       # 256 and 128 tokens a workgroup
+@pytest.mark.parametrize("K", [32, 64, 96, 128, 192])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM])
+def test_gemm_short_reductions(M, N, K, mode):
+    # one to three 64-deep windows per tile: the loads of the window after the last one
+    # (issued at the start of the tile, or by the last window) lie past K and read
+    # nothing the result uses; signed scales take the two-window start, zero points not
+    assert route(M, N, K, 32, 4, mode)[:2] == ("gemm", 256 if M > 128 else 128)
+    w = np.ascontiguousarray(np.resize(rand_w(997, K, seed=K + mode), (N, K)))
+    x = synth.activations(M, K, seed=K)
+    check_matmul(w, x, 32, 4, mode, rows_idx=sample_rows(N, n=64, seed=K), tag=f"gemm {M}x{N}x{K}")
+
+
+GEMM_FORMS = [      # tokens of a workgroup, split, shape (K per group: an odd number of 64-deep steps' halves)
+    (128, False, 102, 4194, {32: 352, 64: 320, 128: 384}),
+    (256, False, 131, 8313, {32: 672, 64: 704, 128: 640}),
+    (128, True, 106, 2235, {32: 6304, 64: 6336, 128: 6272}),
+    (256, True, 409, 882, {32: 9504, 64: 9536, 128: 9472}),
+]
+
+
+@pytest.mark.parametrize("tokens,split,M,N,Ks", GEMM_FORMS)
+@pytest.mark.parametrize("q", [2, 3, 4])
+@pytest.mark.parametrize("group", [32, 64, 128])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_gemm_all_formats(tokens, split, M, N, Ks, q, group, mode):
+    # ragged tiles both ways, whole and cut into slices of K
+    K = Ks[group]
+    r = route(M, N, K, group, q, mode, split)
+    assert r[:2] == ("gemm", tokens) and (r.slices > 1) == split
+    w = np.ascontiguousarray(np.resize(rand_w(min(N, 499), K, seed=q + group), (N, K)))
+    x = synth.activations(M, K, seed=M + mode)
+    check_matmul(w, x, group, q, mode, rows_idx=sample_rows(N, n=40, seed=q), tag=f"gemm {M}x{N}x{K} q{q} g{group}",
+                 workspace=split, repeat=2 if split else 1)
 
 
 @pytest.mark.parametrize("M", [2, 3, 16, 32, 33, 129])
-def test_gemm_small_token_counts(M):
+def test_token_counts_of_every_range(M):
+    # GEMV, exact weights, rounded weights, small tiles
     w = rand_w(64, 512, seed=M)
     x = synth.activations(M, 512, seed=M)
-    check_matmul(w, x, 32, 4, O.SIGNED_SYM, tag=f"gemm M={M}")
+    check_matmul(w, x, 32, 4, O.SIGNED_SYM, tag=f"M={M} 64x512")
 
 
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("mode", MODES)
-def test_gemm_split_reduction_ragged(q, mode):
-    # 4 output tiles (130x200) over K=3104 (97 blocks, 49 steps): split 3 ways, the last
-    # slice carrying the odd half-step; three calls on one workspace
+def test_tile_split_reduction_ragged(q, mode):
+    # 32x32 tiles of 130x200 over K=3104 (97 blocks) in slices of K, the last ending in a unit of
+    # one block; three calls on one workspace
+    assert route(130, 200, 3104, 32, q, mode, True) == ("tile", 32, 32, 4)
     w = rand_w(200, 3104, seed=q + 10 * mode)
     x = synth.activations(130, 3104, seed=q)
     check_matmul(w, x, 32, q, mode, tag="split 130x200x3104", workspace=True, repeat=3)
@@ -270,6 +311,7 @@ def test_gemm_split_last_round(M, N, K, mode):
     # more output tiles than CUs (320, and a ragged 296) with a last round less than half
     # full: those tiles (the weight panels from row 4096 on) are cut into K slices
     # through the workspace while the others are computed whole
+    assert route(M, N, K, 32, 4, mode, True) == ("gemm", 256, 128, 4)
     w = rand_w(N, K, seed=N + mode)
     x = synth.activations(M, K, seed=M)
     rows = np.concatenate([sample_rows(4096, n=8, seed=1), 4096 + sample_rows(N - 4096, n=40, seed=2)])
@@ -281,13 +323,15 @@ def test_gemm_output_past_one_gigabyte():
     """A 4096 x 131072 bf16 output (1 GiB): the GEMM stores it with 64-bit addresses rather
     than through a buffer descriptor; sampled rows against the oracle, guards checked."""
     N, K, M = 131072, 512, 4096
+    assert route(M, N, K, 32, 4, O.SIGNED_SYM).kernel == "gemm"
     w = rand_w(N, K, seed=17)
     x = synth.activations(M, K, seed=17)
     rows = np.concatenate([sample_rows(N, n=24, seed=5), np.array([N - 129, N - 128, N - 127])])
     check_matmul(w, x, 32, 4, O.SIGNED_SYM, rows_idx=np.unique(rows), tag="gemm 4096x131072x512 (1 GiB y)")
 
 
-def test_gemm_split_reduction_eight_ways():
+def test_rounded_split_reduction_group_128():
+    assert route(64, 160, 8192, 128, 4, O.SIGNED_SYM, True) == ("rounded", 64, 16, 4)
     w = rand_w(160, 8192, seed=5)
     x = synth.activations(64, 8192, seed=5)
     check_matmul(w, x, 128, 4, O.SIGNED_SYM, tag="split 64x160x8192", workspace=True, repeat=2)
@@ -295,60 +339,68 @@ def test_gemm_split_reduction_eight_ways():
 
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("mode", MODES)
-def test_skinny_split_reduction_ragged(q, mode):
-    # batched decode with a workspace: N=200 is two 128-row blocks (the second partial),
-    # K=3104 has 25 super-blocks (the last one partial) over 12 slices (the last three
-    # empty); three calls on one workspace
+def test_rounded_with_workspace_ragged(q, mode):
+    # batched decode with a workspace that its cut leaves alone: N=200 ends in half a row tile,
+    # K=3104 in a unit of one block; three calls on one workspace
+    assert route(7, 200, 3104, 32, q, mode, True) == ("rounded", 16, 16, 1)
     w = rand_w(200, 3104, seed=q + 10 * mode + 1)
     x = synth.activations(7, 3104, seed=q + 1)
-    check_matmul(w, x, 32, q, mode, tag="skinny split 7x200x3104", workspace=True, repeat=3)
+    check_matmul(w, x, 32, q, mode, tag="rounded 7x200x3104", workspace=True, repeat=3)
 
 
 @pytest.mark.parametrize("M", [3, 16, 17, 32])
 @pytest.mark.parametrize("group", [32, 128])
-def test_skinny_split_token_counts(M, group):
+def test_streaming_split_token_counts(M, group):
+    # exact weights up to 16 tokens, rounded above, four slices of K
+    assert route(M, 300, 8192, group, 4, O.ASYM, True).slices > 1
     w = rand_w(300, 8192, seed=M + group)
     x = synth.activations(M, 8192, seed=M + group)
     for mode in MODES:
-        check_matmul(w, x, group, 4, mode, tag=f"skinny split M={M}", workspace=True, repeat=2)
+        check_matmul(w, x, group, 4, mode, tag=f"streaming split M={M}", workspace=True, repeat=2)
 
 
-# Activation-stationary batched decode (q = 2, 4; K a multiple of the wavefront range).
+# Exact weights (q = 2, 4; up to 16 tokens; K a multiple of 512).
 
 @pytest.mark.parametrize("M", [5, 16])
 @pytest.mark.parametrize("q", [2, 4])
 @pytest.mark.parametrize("group", [32, 64, 128])
 @pytest.mark.parametrize("mode", MODES)
-def test_stationary_all_formats(M, q, group, mode):
-    # N=45: three 16-row tiles, the last one partial.  K=2560: five 512-wide ranges, two
-    # slices of four wavefronts (the second with one live); two calls on one workspace
-    assert exact_weight_path(M, 2560, q, True)
+def test_exact_all_formats(M, q, group, mode):
+    # N=45: three 16-row tiles, the last one partial.  K=2560: ten units over eight wavefronts;
+    # two calls on one workspace
+    assert route(M, 45, 2560, group, q, mode, True).kernel == "exact"
     w = rand_w(45, 2560, seed=100 + 7 * q + group + mode + M)
     x = synth.activations(M, 2560, seed=q * group + M)
-    check_matmul(w, x, group, q, mode, tag=f"stationary {M}x45x2560", workspace=True, repeat=2)
+    check_matmul(w, x, group, q, mode, tag=f"exact {M}x45x2560", workspace=True, repeat=2)
 
 
 @pytest.mark.parametrize("q", [2, 4])
 @pytest.mark.parametrize("M,N,K,workspace", [
-    (16, 6400, 4096, True),     # two slices, 400 tiles: runs of two tiles
-    (9, 9600, 6144, True),      # three slices, 600 tiles: runs of four, the last one short
-    (13, 4100, 3072, True),     # a 4-row last tile and a tile past N in the last run
-    (16, 2000, 1024, False),    # one slice (two live wavefronts): no workspace, y per tile
+    (16, 6400, 4096, True),     # 400 tiles, two a workgroup
+    (9, 9600, 6144, True),      # 600 tiles, three a workgroup
+    (13, 4100, 3072, True),     # a 4-row last tile and a tile past N
+    (16, 2000, 1024, False),    # four units: half of the wavefronts without work
 ])
-def test_stationary_runs(q, M, N, K, workspace):
-    assert exact_weight_path(M, K, q, workspace)
+def test_exact_row_tiles(q, M, N, K, workspace):
+    assert route(M, N, K, 32, q, O.SIGNED_SYM, workspace).kernel == "exact"
     w = rand_w(N, K, seed=N + K + q)
     x = synth.activations(M, K, seed=M + q)
     for mode in (O.SIGNED_SYM, O.ASYM_MIN):
-        check_matmul(w, x, 32, q, mode, rows_idx=sample_rows(N, n=48, seed=q), tag=f"stationary runs {M}x{N}x{K}",
+        check_matmul(w, x, 32, q, mode, rows_idx=sample_rows(N, n=48, seed=q), tag=f"exact row tiles {M}x{N}x{K}",
                      workspace=workspace, repeat=2 if workspace else 1, need_split=False)
 
 
-@pytest.mark.parametrize("M,N,K", [(96, 256, 8192), (300, 256, 8192), (16, 256, 8192)])
+@pytest.mark.parametrize("M,N,K", [
+    (96, 256, 8192), (300, 256, 8192),           # small tiles
+    (16, 256, 8192),                             # streaming, exact weights
+    (106, 2235, 6272), (409, 882, 9472),         # GEMM, 128 and 256 tokens a workgroup
+    (16, 23000, 6656), (24, 18500, 4224),        # large matrices, exact and rounded
+])
 def test_split_reduction_graph_replay(M, N, K):
     """The split kernels in a HIP graph: the arrival counters reset inside the kernel, so
     every replay (with eager work between) reproduces the first result."""
-    w = rand_w(N, K, seed=8)
+    assert route(M, N, K, 32, 4, O.SIGNED_SYM, True).slices > 1
+    w = np.ascontiguousarray(np.resize(rand_w(min(N, 256), K, seed=8), (N, K)))
     W = to_device(w, True)
     codes, scales, _ = ssq.ssq_quantize(W, 32, 4, O.SIGNED_SYM)
     x_host = synth.activations(M, K, seed=8)
@@ -356,8 +408,9 @@ def test_split_reduction_graph_replay(M, N, K):
     ws = ssq.ssq_matmul_workspace(M, N, K, 32, 4)
     assert ws is not None
     y_eager = ssq.ssq_matmul(x, codes, scales, None, N, K, 32, 4, workspace=ws)
-    ref_q = O.quantize(widen(w, True), 32, 4, O.SIGNED_SYM)
-    compare_matmul(y_eager, widen(x_host, True), ref_q, np.arange(N), K, 32, 4, True, f"graph split M={M}",
+    sel = np.arange(N) if N <= 256 else sample_rows(N, n=64, seed=M)
+    ref_q = O.quantize(widen(w[sel], True), 32, 4, O.SIGNED_SYM)
+    compare_matmul(y_eager, widen(x_host, True), ref_q, sel, K, 32, 4, True, f"graph split M={M}",
                    workspace=True)
     y = torch.empty_like(y_eager)
     ssq.ssq_matmul(x, codes, scales, None, N, K, 32, 4, out=y, workspace=ws)
@@ -565,6 +618,16 @@ def test_f32_matmul_edges(M, N, K, q, mode):
     check_matmul(w, x, 32, q, mode, bf16_w=False, bf16_x=False, tag=f"f32 {M}x{N}x{K}")
 
 
+@pytest.mark.parametrize("M,N,K", [(4, 40, 896), (8, 33, 2432), (17, 50, 1152)])       # 4, 8 and 16 tokens a stage
+@pytest.mark.parametrize("q", [2, 3, 4])
+@pytest.mark.parametrize("group", [64, 128])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_f32_matmul_groups(M, N, K, q, group, mode):
+    w = rand_w(N, K, seed=M + N + q, bf16=False)
+    x = synth.activations(M, K, seed=M + mode, bf16=False)
+    check_matmul(w, x, group, q, mode, bf16_w=False, bf16_x=False, tag=f"f32 {M}x{N}x{K} g{group}")
+
+
 @pytest.mark.parametrize("M,N,K,workspace", [
     (1, 45, 1536, False), (2, 45, 1536, False),                                    # GEMV
     (5, 45, 1536, False), (16, 4500, 512, False), (9, 45, 2560, True),             # exact weights
@@ -577,6 +640,7 @@ def test_zero_points_past_the_code_range(M, N, K, workspace, q):
     makes): odd ones from 129 on, whose 128 + z has nine significant bits."""
     rng = np.random.default_rng(M + N + q)
     ref_q = O.quantize(widen(rand_w(min(N, 97), K, seed=M + q), True), 32, q, O.ASYM)
+    assert N != 8192 or route(M, N, K, 32, q, O.ASYM, workspace).kernel == "stat"
     ref_q.zp[:] = rng.integers(64, 128, size=ref_q.zp.shape) * 2 + 1
     rows = np.resize(np.arange(len(ref_q.zp)), N)
     dev = [torch.from_numpy(np.ascontiguousarray(a[rows])).cuda() for a in (ref_q.codes, ref_q.scales.view(np.int16), ref_q.zp)]
@@ -592,27 +656,31 @@ def test_zero_points_past_the_code_range(M, N, K, workspace, q):
 
 # ---------------------------------------------------------------------------
 # Streaming kernels (3 <= M <= 80): every tile of tokens (8 to 80) and every number of
-# 16-row tiles per workgroup, sliced and not, and the large matrices that go to the kernels
-# cut across small workgroups instead.
+# 16-row tiles per workgroup, with all of K in a workgroup and in slices, and the large
+# matrices that go to the kernels cut across small workgroups instead.
 # ---------------------------------------------------------------------------
-@pytest.mark.parametrize("M,N,K,workspace", [
+STREAMING = [
     # exact weights, 8 tokens: 1, 2 (a short last tile), 3 and 4 row tiles a workgroup
     (5, 17, 512, False), (8, 4100, 1536, False), (5, 9000, 1024, False), (3, 12300, 1024, False),
-    # 16 tokens: 2 to 4 row tiles, four slices of K, one slice
+    # 16 tokens: 2 to 4 row tiles, four slices of K, a workspace left alone
     (16, 4500, 512, False), (9, 8200, 512, False), (13, 12500, 512, False), (16, 200, 8192, True),
     (11, 3000, 4608, True),
     # rounded weights; 9 or 17 blocks of K: a unit of one block after one or two full ones
-    (7, 50, 288, False), (16, 4097, 544, False), (10, 9000, 800, False), (14, 70, 4128, True),
+    (7, 50, 288, False), (16, 4097, 544, False), (10, 9000, 800, False), (12, 12500, 800, False), (14, 70, 4128, True),
     (17, 4090, 544, False), (25, 8100, 320, False), (32, 12200, 320, False), (20, 16001, 288, False),
     (31, 20000, 288, False), (24, 1000, 4128, True),
     (33, 4000, 288, False), (48, 7000, 288, False), (40, 16000, 288, False), (40, 300, 8192, True),
     (49, 3000, 288, False), (64, 8100, 544, False), (50, 15000, 288, False), (64, 520, 4128, True),
     (65, 3001, 288, False), (79, 8000, 288, False), (80, 12000, 1056, False), (66, 16000, 1056, False), (70, 16000, 288, False),
-    (77, 200, 4352, True), (81, 200, 4352, True),
+    (77, 200, 4352, True), (81, 200, 4352, True),                # 81 tokens: a small tile
     # more than 1024 row tiles: exact in one slice, exact in several, rounded
     (13, 18500, 1024, False), (16, 23000, 6656, True), (24, 18500, 4128, True), (7, 18500, 4128, True),
-])
-@pytest.mark.parametrize("q,mode", [(2, O.SIGNED_SYM), (3, O.ASYM), (4, O.ASYM_MIN), (4, O.SIGNED_SYM)])
+]
+STREAMING_FORMATS = [(2, O.SIGNED_SYM), (3, O.ASYM), (4, O.ASYM_MIN), (4, O.SIGNED_SYM)]
+
+
+@pytest.mark.parametrize("M,N,K,workspace", STREAMING)
+@pytest.mark.parametrize("q,mode", STREAMING_FORMATS)
 def test_streaming_tiles(M, N, K, workspace, q, mode):
     w = rand_w(min(N, 997), K, seed=M + N + q)
     w = np.ascontiguousarray(np.resize(w, (N, K)))          # 997 rows, repeated
@@ -621,23 +689,96 @@ def test_streaming_tiles(M, N, K, workspace, q, mode):
                  workspace=workspace, repeat=2 if workspace else 1, need_split=False)
 
 
+# Several row tiles a workgroup and several slices of K, in every group size: exact weights of 8
+# and 16 tokens, rounded ones of 16 to 80.
+STREAMING_SLICES = [
+    (4, 33, 4608), (4, 1474, 10240), (6, 1608, 14336), (4, 2233, 13824),
+    (9, 35, 4608), (11, 1085, 12800), (16, 1232, 12800), (10, 4265, 5632),
+    (13, 1396, 8576), (4, 1849, 8320), (8, 4292, 4736),
+    (20, 34, 2176), (20, 1482, 4224), (20, 2139, 6272), (23, 4101, 4224), (18, 3478, 8576),
+    (35, 33, 2176), (40, 1364, 4224), (33, 1656, 8320),
+    (49, 33, 2176), (50, 2168, 2176), (50, 2729, 4224),
+    (65, 38, 2176), (66, 1051, 6272), (65, 1399, 10368),
+]
+SLICE_FORMATS = [(2, 64, O.ASYM), (3, 128, O.SIGNED_SYM), (3, 64, O.ASYM_MIN), (4, 128, O.ASYM), (4, 64, O.SIGNED_SYM), (4, 32, O.ASYM_MIN)]
+
+
+@pytest.mark.parametrize("M,N,K", STREAMING_SLICES)
+@pytest.mark.parametrize("q,group,mode", SLICE_FORMATS)
+def test_streaming_slices(M, N, K, q, group, mode):
+    r = route(M, N, K, group, q, mode, True)
+    assert r.kernel in ("exact", "rounded")
+    assert r.slices > 1 or mode != O.SIGNED_SYM       # 80 rows with metadata do not fit the LDS
+    w = np.ascontiguousarray(np.resize(rand_w(min(N, 211), K, seed=M + N + q), (N, K)))
+    x = synth.activations(M, K, seed=M + mode)
+    check_matmul(w, x, group, q, mode, rows_idx=sample_rows(N, n=48, seed=q), tag=f"slices {M}x{N}x{K} q{q} g{group}",
+                 workspace=True, repeat=2)
+
+
+# Large matrices (skinny.hip): more than 1024 row tiles, every group size and layout.
+LARGE = [
+    ("stat", 13, 16500, 1024, False), ("stat", 15, 17203, 9216, True),      # exact: one slice of K, five
+    ("split", 7, 16431, 1152, True), ("split", 24, 17408, 7168, True),      # rounded: 16 and 32 tokens
+]
+
+
+LARGE_FORMATS = [(32, O.ASYM), (64, O.SIGNED_SYM), (64, O.ASYM_MIN), (128, O.SIGNED_SYM), (128, O.ASYM), (128, O.ASYM_MIN)]
+# 3-bit weights are never exact, and those with metadata may stream at more than 16 tokens
+LARGE_CASES = [(*case, q, group, mode) for case in LARGE for q in (2, 3, 4) for group, mode in LARGE_FORMATS
+               if q != 3 or (case[0] == "split" and (case[1] <= 16 or group == 128 or mode == O.SIGNED_SYM))]
+
+
+@pytest.mark.parametrize("kernel,M,N,K,workspace,q,group,mode", LARGE_CASES)
+def test_large_matrices(kernel, M, N, K, workspace, q, group, mode):
+    r = route(M, N, K, group, q, mode, workspace)
+    assert r.kernel == kernel and (r.slices > 1) == workspace
+    w = np.ascontiguousarray(np.resize(rand_w(499, K, seed=M + N + q), (N, K)))
+    x = synth.activations(M, K, seed=M + mode)
+    check_matmul(w, x, group, q, mode, rows_idx=sample_rows(N, n=48, seed=q), tag=f"{kernel} {M}x{N}x{K} q{q} g{group}",
+                 workspace=workspace, repeat=2 if workspace else 1, need_split=False)
+
+
 # ---------------------------------------------------------------------------
 # Middle token counts: small tiles whose wavefronts split K, 32 x 32 to 128 x 64, unsliced
 # and in slices of K; ragged rows and tokens; units of one block, units without work.
 # ---------------------------------------------------------------------------
-@pytest.mark.parametrize("M,N,K,workspace", [
+MIDDLE = [
     (81, 300, 1056, False), (83, 500, 8192, True),              # 32 tokens x 32 rows
     (100, 40, 288, False), (160, 2050, 2080, False), (120, 500, 16416, True),    # 64 x 32
     (95, 8100, 1056, False), (190, 600, 4128, True),            # 96 x 32
     (250, 4000, 1056, False), (200, 900, 12288, True),          # 64 x 64
     (350, 4070, 2080, False), (147, 2500, 8224, True),          # 96 x 64
-    (300, 4100, 2336, False), (128, 12200, 1056, False),        # 128 x 64
-    (64, 9000, 3424, True),                                     # from the streaming range
-])
+    (300, 4100, 2336, False), (213, 1379, 7680, True),          # 128 x 64
+    (64, 9000, 3424, True),                                     # from the streaming range: 64 x 64
+    (128, 12200, 1056, False),                                  # past them: the GEMM
+]
+
+
+@pytest.mark.parametrize("M,N,K,workspace", MIDDLE)
 @pytest.mark.parametrize("q,group,mode", [(2, 32, O.ASYM), (3, 32, O.SIGNED_SYM), (4, 32, O.ASYM_MIN), (4, 32, O.SIGNED_SYM)])
 def test_middle_tiles(M, N, K, workspace, q, group, mode):
     w = rand_w(min(N, 997), K, seed=M + N + q)
     w = np.ascontiguousarray(np.resize(w, (N, K)))
     x = synth.activations(M, K, seed=M + mode)
     check_matmul(w, x, group, q, mode, rows_idx=sample_rows(N, n=64, seed=q), tag=f"middle {M}x{N}x{K} q{q}",
+                 workspace=workspace, repeat=2 if workspace else 1, need_split=False)
+
+
+# The same tiles in the other group sizes: K of whole groups, units partly filled.
+MIDDLE_GROUPS = [
+    (81, 300, 1152, False), (83, 500, 8320, True), (160, 2050, 2176, False), (120, 500, 16512, True),
+    (95, 8100, 1152, False), (190, 600, 4224, True), (250, 4000, 1152, False), (200, 900, 12416, True),
+    (350, 4070, 2176, False), (147, 2500, 8320, True), (300, 4100, 2432, False), (213, 1379, 7680, True),
+]
+
+
+@pytest.mark.parametrize("M,N,K,workspace", MIDDLE_GROUPS)
+@pytest.mark.parametrize("q,group,mode", [(2, 64, O.SIGNED_SYM), (2, 128, O.ASYM_MIN), (3, 64, O.ASYM), (3, 128, O.ASYM_MIN),
+                                          (4, 64, O.ASYM_MIN), (4, 128, O.ASYM)])
+def test_middle_tiles_groups(M, N, K, workspace, q, group, mode):
+    r = route(M, N, K, group, q, mode, workspace)
+    assert r.kernel == "tile" and (r.slices > 1) == workspace
+    w = np.ascontiguousarray(np.resize(rand_w(min(N, 499), K, seed=M + N + q), (N, K)))
+    x = synth.activations(M, K, seed=M + mode)
+    check_matmul(w, x, group, q, mode, rows_idx=sample_rows(N, n=48, seed=q), tag=f"middle {M}x{N}x{K} q{q} g{group}",
                  workspace=workspace, repeat=2 if workspace else 1, need_split=False)

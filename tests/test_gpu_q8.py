@@ -9,6 +9,7 @@ import torch
 
 from oracle import ssq_oracle as O
 from paper_2607_08779_amd import ssq, synth
+from tests.routes import route
 from tests.parity_common import (Guarded, assert_within, log_metric, rel_l2, sample_rows, to_device,
                                  y_to_f64)
 
@@ -63,10 +64,16 @@ def test_quantize_act_q8_worked_example_and_edges():
     check_act(bf16_bits(np.stack(rows)), tag="edges")
 
 
-def check_q8_matmul(w, x_bits, group, q, mode, rows_idx=None, tag=""):
-    """Oracle-quantized weights and activations on the GPU through ssq_matmul_q8."""
+def check_q8_matmul(w, x_bits, group, q, mode, rows_idx=None, tag="", repeat_rows=None):
+    """Oracle-quantized weights and activations on the GPU through ssq_matmul_q8.  The rows of w
+    come round until there are `repeat_rows`."""
     N, K = w.shape
     r = O.quantize(w, group, q, mode)
+    if repeat_rows is not None:
+        at = np.resize(np.arange(N), repeat_rows)
+        N = repeat_rows
+        r = r._replace(codes=r.codes[at], scales=r.scales[at], zp=None if r.zp is None else r.zp[at],
+                       mins=None if r.mins is None else r.mins[at])
     a = O.quantize_act_q8(O.bf16_bits_to_f32(x_bits))
     meta = r.mins if mode == O.ASYM_MIN else r.zp
     dev_meta = None if meta is None else torch.from_numpy(
@@ -141,14 +148,16 @@ def test_q8_pipeline_llama3_8b_down_proj_full_size():
 
 
 # ---------------------------------------------------------------------------
-# Batched decode (2 <= M <= 32 per launch, integer MFMA, one read of the weights).
+# Several tokens: the one-token kernel with a grid row per token (up to 16 tokens of small
+# matrices) and the smallest tile.
 # ---------------------------------------------------------------------------
 
 @pytest.mark.parametrize("M", [2, 16, 17, 32, 33, 40])
 @pytest.mark.parametrize("mode", MODES)
 def test_matmul_q8_batched_token_counts(M, mode):
-    """One and two 16-token tiles, and more than 32 tokens (launches of 32 and the rest);
-    70 rows (a ragged last 16-row workgroup) and K = 2016 (63 blocks: a ragged last quad)."""
+    """Up to 16 tokens the one-token kernel, above 32x32 tiles, one and two of them; 70 rows (a
+    ragged last tile) and K = 2016 (63 blocks: a ragged last stage)."""
+    assert route(M, 70, 2016, 32, 4, mode, q8=True).kernel == ("q8_gemv" if M <= 16 else "q8_tile")
     rng = np.random.default_rng(M * 5 + mode)
     w = O.bf16_bits_to_f32(bf16_bits(rng.standard_t(5, size=(70, 2016)) * 0.02))
     check_q8_matmul(w, act_bits(M, 2016, seed=M + 100), 32, 4, mode, tag=f"batched M={M} m={mode}")
@@ -157,7 +166,8 @@ def test_matmul_q8_batched_token_counts(M, mode):
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("group", [32, 64, 128])
 def test_matmul_q8_batched_formats(q, group):
-    """Every q and group size at M = 16 with K = 4224 (33 quads over 16 wavefronts)."""
+    """Every q and group size at M = 16 with K = 4224: the one-token kernel, a grid row a token."""
+    assert route(16, 33, 4224, group, q, O.ASYM, q8=True).kernel == "q8_gemv"
     rng = np.random.default_rng(q * 13 + group)
     w = O.bf16_bits_to_f32(bf16_bits(rng.standard_t(5, size=(33, 4224)) * 0.02))
     for mode in MODES:
@@ -166,8 +176,7 @@ def test_matmul_q8_batched_formats(q, group):
 
 
 def test_matmul_q8_batched_long_rows_fall_back():
-    """K past the batched kernel's token-scale staging (K > 32768) takes the one-token
-    kernel per token; same answers."""
+    """Rows longer than K = 32768 take the one-token kernel per token; same answers."""
     rng = np.random.default_rng(77)
     w = O.bf16_bits_to_f32(bf16_bits(rng.standard_t(5, size=(9, 33792)) * 0.02))
     check_q8_matmul(w, act_bits(3, 33792, seed=78), 32, 4, O.SIGNED_SYM, tag="batched K=33792")
@@ -175,7 +184,7 @@ def test_matmul_q8_batched_long_rows_fall_back():
 
 @pytest.mark.parametrize("M", [16, 32])
 def test_q8_batched_llama3_8b_down_proj_full_size(M):
-    """4096x14336 at W4 g32, signed, M tokens through one read of the weights, sampled rows."""
+    """4096x14336 at W4 g32, signed, M tokens in 32x32 tiles, sampled rows."""
     spec = synth.llama3_8b_decode().layers["down_proj"]
     wb = synth.weights(spec)
     x = act_bits(M, spec.cols, seed=31 + M, scale=0.5)
@@ -196,13 +205,16 @@ def test_q8_batched_llama3_8b_down_proj_full_size(M):
 # outputs, chosen by how many of each cover M x N.
 # ---------------------------------------------------------------------------
 
-@pytest.mark.parametrize("M,N,K", [
-    (3, 33, 544),        # 32x32: a ragged tile both ways, two 512-deep stages, the second one block
+Q8_TILES = [
+    (3, 33, 544),        # too few tokens for a tile: the one-token kernel
     (31, 8225, 288),     # 32x64: the last tile one column; two 256-deep stages, the second one block
     (65, 8161, 800),     # 64x64: two token tiles, the second one row; four stages, the last one block
     (129, 10400, 256),   # 64x128: three token tiles; exactly one stage
     (255, 14305, 1056),  # 128x128: two token tiles, the second short of a row; five stages
-])
+]
+
+
+@pytest.mark.parametrize("M,N,K", Q8_TILES)
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
 def test_matmul_q8_tiles(M, N, K, q, mode):
@@ -212,15 +224,37 @@ def test_matmul_q8_tiles(M, N, K, q, mode):
                     tag=f"tiles {M}x{N}x{K} q={q} m={mode}")
 
 
+# The same tiles in the other group sizes, and 32x32 with two workgroups a CU.
+@pytest.mark.parametrize("tile,M,N,K", [
+    ((32, 32), 17, 33, 640),         # two 512-deep stages, the second four blocks
+    ((32, 32), 16, 17000, 640),      # 532 tiles
+    ((32, 64), 31, 8225, 384),
+    ((64, 64), 65, 8161, 896),
+    ((64, 128), 129, 10400, 1152),
+    ((128, 128), 255, 14305, 1152),
+])
+@pytest.mark.parametrize("q", [2, 3, 4])
+@pytest.mark.parametrize("group", [64, 128])
+@pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
+def test_matmul_q8_tile_groups(tile, M, N, K, q, group, mode):
+    assert route(M, N, K, group, q, mode, q8=True)[:3] == ("q8_tile", *tile)
+    w = O.bf16_bits_to_f32(synth.weights(synth.WeightSpec(min(N, 499), K, nu=5.0, scale=0.02, outlier_frac=0.001, seed=M + q)))
+    check_q8_matmul(w, act_bits(M, K, seed=M + mode), group, q, mode, rows_idx=sample_rows(N, n=40, seed=q),
+                    tag=f"tiles {M}x{N}x{K} q={q} g={group} m={mode}", repeat_rows=N)
+
+
 # Few tokens: the one-token kernel with a grid row per token on small or long matrices, and
-# the 32x32 tile just past its 16 tokens and on a matrix large enough for the tile at 8.
-@pytest.mark.parametrize("M,N,K", [
-    (2, 5, 32),          # one block, a row past the workgroup's four
+# the tiles just past its 16 tokens and on a matrix large enough for them at 8.
+Q8_FEW = [
+    (2, 5, 32),          # one block: a 32x32 tile, as the one-token kernel would gain nothing
     (3, 1001, 4128),     # 129 blocks: ragged passes over K
     (16, 130, 8224),     # its most tokens, ragged rows
     (17, 33, 544),       # 32x32: a ragged tile both ways, two stages, the second one block
-    (8, 8200, 544),      # 32x32: 257 tiles, two workgroups a CU
-])
+    (8, 8200, 544),      # 32x64
+]
+
+
+@pytest.mark.parametrize("M,N,K", Q8_FEW)
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
 def test_matmul_q8_few_tokens(M, N, K, q, mode):

@@ -1,0 +1,63 @@
+"""Which kernels the GPU tests reach, asked of the library on the host: every form of the
+several-token matmul kernels that a call can reach must be in some test's list, whole and in
+slices of K where it has both."""
+import functools
+import random
+
+import pytest
+
+from oracle import ssq_oracle as O
+from tests import test_gpu_matmul as gm, test_gpu_q8 as gq
+from tests.routes import route
+
+
+@functools.lru_cache(None)
+def covered():
+    seen = set()
+    for M, N, K, workspace in gm.STREAMING:
+        for q, mode in gm.STREAMING_FORMATS:
+            seen.add((q, route(M, N, K, 32, q, mode, workspace)))
+    for M, N, K in gm.STREAMING_SLICES:
+        for q, group, mode in gm.SLICE_FORMATS:
+            seen.add((q, route(M, N, K, group, q, mode, True)))
+    for _, M, N, K, workspace in gm.LARGE:
+        for q in (2, 3, 4):
+            seen.add((q, route(M, N, K, 128, q, O.SIGNED_SYM, workspace)))
+    for M, N, K, workspace in gm.MIDDLE + gm.MIDDLE_GROUPS:
+        for q in (2, 3, 4):
+            seen.add((q, route(M, N, K, 32, q, O.SIGNED_SYM, workspace)))
+    for _, split, M, N, Ks in gm.GEMM_FORMS:
+        for q in (2, 3, 4):
+            seen.add((q, route(M, N, Ks[64], 64, q, O.SIGNED_SYM, split)))
+    return {form(q, r) for q, r in seen}
+
+
+def form(q, r):
+    """The compiled kernel, and whether its slices meet in the workspace.  Row tiles of a run of
+    the exact kernel for large matrices are a loop, not a form."""
+    return q, r.kernel, r.tokens, 0 if r.kernel == "stat" else r.rows, r.slices > 1
+
+
+def test_every_reachable_form_is_tested():
+    rng = random.Random(3)
+    reached = {}
+    for _ in range(60000):
+        M = rng.choice((rng.randint(3, 80), rng.randint(3, 80), rng.randint(81, 2100)))
+        N = int(2 ** rng.uniform(4, 15.2))
+        K = 512 * rng.randint(1, 56) if rng.random() < 0.5 else 128 * rng.randint(1, 224)
+        q, mode = rng.choice((2, 3, 4)), rng.choice((O.SIGNED_SYM, O.ASYM, O.ASYM_MIN))
+        r = route(M, N, K, 128, q, mode, rng.random() < 0.8)
+        reached.setdefault(form(q, r), (M, N, K, mode))
+    missing = {f: s for f, s in reached.items() if f not in covered()}
+    assert not missing, missing
+
+
+@pytest.mark.parametrize("shapes,kernels", [
+    (gq.Q8_TILES, ["q8_gemv", "q8_tile 32x64", "q8_tile 64x64", "q8_tile 64x128", "q8_tile 128x128"]),
+    (gq.Q8_FEW, ["q8_tile 32x32", "q8_gemv", "q8_gemv", "q8_tile 32x32", "q8_tile 32x64"]),
+])
+def test_q8_shapes_run_what_their_comments_say(shapes, kernels):
+    for (M, N, K), want in zip(shapes, kernels):
+        for q in (2, 3, 4):
+            r = route(M, N, K, 32, q, O.SIGNED_SYM, q8=True)
+            assert (r.kernel if r.kernel == "q8_gemv" else f"{r.kernel} {r.tokens}x{r.rows}") == want, (M, N, K, q)

@@ -28,13 +28,17 @@ def run_noalloc(x, codes, scales, zp, N, K, group, q, y):
 
 
 CASES = [
-    # (M, N, K, q, group, mode, weight seed): prefill headline (GEMM split 4 ways), a ragged
-    # GEMM split, batched decode split, a plain GEMV (no scratch), batched decode split again
+    # (M, N, K, q, group, mode, weight seed): prefill headline (GEMM split 4 ways), small tiles
+    # in slices, streaming in slices, a plain GEMV (no scratch), streaming with a scratch that
+    # it leaves alone, a ragged GEMM split, a large matrix split exactly, and rounded
     (512, 4096, 14336, 4, 32, O.SIGNED_SYM, 4006),
     (130, 200, 3104, 3, 32, O.ASYM, 11),
     (16, 300, 8192, 4, 32, O.SIGNED_SYM, 12),
     (1, 96, 1024, 2, 64, O.SIGNED_SYM, 13),
     (7, 200, 3072, 2, 128, O.UNSIGNED_SYM, 14),
+    (106, 2235, 6336, 3, 64, O.ASYM, 15),
+    (15, 17203, 9216, 4, 128, O.SIGNED_SYM, 16),
+    (7, 16431, 1152, 3, 64, O.ASYM, 17),
 ]
 
 
