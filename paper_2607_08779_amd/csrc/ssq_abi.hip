@@ -261,7 +261,7 @@ int ssq_internal_route(int64_t M, int64_t N, int64_t K, int group, int q, int ki
   const int64_t have = (int64_t)workspace_bytes;
   const ssq::Route r = q8 ? ssq::q8_route(M, N, K, q)
                      : M <= 2 ? ssq::Route{ssq::kRouteGemv, (int)M, 0, 1}
-                     : M <= ssq::kStreamMaxM ? ssq::stream_route(M, N, K, q, kind, aligned != 0, have)
+                     : M <= ssq::kStreamMaxM ? ssq::stream_route(M, N, K, group, q, kind, aligned != 0, have)
                                              : ssq::gemm_route(M, N, K, q, have);
   out[0] = r.kernel; out[1] = r.tokens; out[2] = r.rows; out[3] = r.slices;
   return SSQ_OK;

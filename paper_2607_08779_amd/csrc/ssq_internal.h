@@ -228,7 +228,7 @@ enum RouteKernel : int { kRouteGemv = 0, kRouteExact, kRouteRounded, kRouteStat,
 struct Route {
   int kernel, tokens, rows, slices;
 };
-Route stream_route(int64_t M, int64_t N, int64_t K, int q, int kind, bool aligned, int64_t workspace_bytes);
+Route stream_route(int64_t M, int64_t N, int64_t K, int group, int q, int kind, bool aligned, int64_t workspace_bytes);
 Route skinny_route(int64_t M, int64_t N, int64_t K, int q, bool exact);
 Route gemm_route(int64_t M, int64_t N, int64_t K, int q, int64_t workspace_bytes);
 Route q8_route(int64_t M, int64_t N, int64_t K, int q);

@@ -89,6 +89,27 @@ Cut choose(const Form& f, bool exact, int64_t N, int64_t K, int q, int kind, int
   return best;
 }
 
+// 3-bit codes at 17 to 32 tokens over 1024 row tiles: the streaming kernel is faster than the one
+// cut across small workgroups where its rounds are full (1280 tiles are one round of five a
+// workgroup, 1536 two of three) and rows are short or, with zero points or minimums in groups
+// of 32 or 64, longer too.  That one / streaming, us, 24 tokens (17 and 32 alike):
+//   no metadata, up to 1280 tiles: 18432x1024 13.2 / 9.2, 20480x2048 16.6 / 13.6, 18432x4096
+//     28.2 / 24.0, 20480x5120 33.1 / 28.3, 19456x4608 26.2 / 26.5, 17408x5120 26.9 / 27.6, but
+//     19456x5632 30.9 / 32.7, 16448x7168 33.1 / 35.4, 20480x8192 40.7 / 42.7;
+//   up to 1536: 22016x3072 27.1 / 22.2, 24576x2048 19.6 / 17.3, but 22016x4096 26.1 / 29.2,
+//     24576x4096 27.2 / 30.4; more: 28672x2048 19.8 / 21.0, 28672x4096 32.9 / 37.4,
+//     32768x3072 27.0 / 29.1;
+//   zero points, groups of 32 (minimums alike): 17408x5120 31.4 / 29.0, 20480x6144 39.4 / 35.5,
+//     16448x8192 47.8 / 45.2, 24576x6144 49.2 / 45.7, but 18432x12288 64.4 / 66.2, 24576x4096
+//     31.7 / 33.0, 28672x4608 43.6 / 45.0, 28672x8192 68.2 / 72.2;
+//   groups of 64: 17408x5120 29.7 / 27.9, 20480x6144 37.3 / 34.9, 24576x4096 29.3 / 31.3;
+//   groups of 128 as no metadata: 20480x5120 32.9 / 28.0, 16448x8192 42.1 / 43.2.
+bool three_bits_stream(int64_t tiles, int64_t K, int64_t weights, int group, int kind) {
+  const bool meta = kind != 0 && group < 128 && weights < 190000000;
+  if (tiles <= 1280) return K <= 5120 || meta;
+  return tiles <= 1536 && (K <= 3072 || (meta && group == 32 && K > 4096));
+}
+
 // Large matrices go to the kernels that cut K across many small workgroups (skinny.hip) where
 // those measured faster, a workspace given (W4 g32 signed unless said, us, those / these).
 // Their time follows the weights; that of these follows rounds of 256 workgroups of up to
@@ -96,7 +117,7 @@ Cut choose(const Form& f, bool exact, int64_t N, int64_t K, int q, int kind, int
 //   over 1024 tiles, exact from 1.5e8 weights on: 16 tokens on 28672x8192 36.7 / 42.8,
 //     24576x8192 33.2 / 36.3, but 28672x4096 26.6 / 23.8; rounded always: 24 tokens on
 //     28672x8192 50.2 / 62.1, 28672x4096 31.2 / 34.3, except 3-bit codes at 17 to 32 tokens
-//     below 1.2e8 weights: 17408x5120 31.4 / 28.9;
+//     (three_bits_stream);
 //   513 to 1024 tiles, from 1.9e8 weights on: 16 tokens on 13312x16384 39.0 / 44.1 (but
 //     13312x12288 30.7 / 31.0); at 17 to 32 tokens from 1.2e8 on, 3-bit codes excepted:
 //     32 tokens on 10240x12288 31.6 / 35.6, W2 27.9 / 32.8, W3 40.9 / 41.4, but 13312x8192
@@ -104,11 +125,11 @@ Cut choose(const Form& f, bool exact, int64_t N, int64_t K, int q, int kind, int
 //   exact over a K of one slice (no workspace needed): over 1024 tiles, and from 512 on
 //     where groups hold a minimum or zero point: 12 tokens on 28672x2048 10.8 / 13.9,
 //     W4 asymmetric on 8192x2048 6.1 / 6.8.
-bool blocked_is_faster(int64_t M, int64_t N, int64_t K, int q, int kind, bool exact, bool workspace) {
+bool blocked_is_faster(int64_t M, int64_t N, int64_t K, int group, int q, int kind, bool exact, bool workspace) {
   const int64_t tiles = (N + 15) / 16, weights = N * K;
   if (exact && K <= 2048) return tiles > 1024 || (kind != 0 && K > 1024 && tiles >= 512);
   if (!workspace || M > kSkinnyMaxM || tiles <= 512) return false;
-  if (tiles > 1024) return exact ? weights >= 150000000 : !(q == 3 && M > 16 && weights < 120000000);
+  if (tiles > 1024) return exact ? weights >= 150000000 : !(q == 3 && M > 16 && three_bits_stream(tiles, K, weights, group, kind));
   if (M > 16 && q != 3 && weights >= 120000000) return q == 4 || tiles < 900;
   return weights >= 190000000 && !(M > 16 && tiles >= 900) && !(q == 2 && tiles >= 900);
 }
@@ -147,7 +168,7 @@ struct Choice {
   Cut cut;
   TilePlan tile;
 };
-Choice choose_kernel(int64_t M, int64_t N, int64_t K, int q, int kind, bool aligned, int64_t have) {
+Choice choose_kernel(int64_t M, int64_t N, int64_t K, int group, int q, int kind, bool aligned, int64_t have) {
   // Exact weights: the sizes that allow it, rows of scales and metadata that start 16-byte
   // aligned, and the workspace its layout names (or a K that needs none).
   int64_t exact_bytes = 0;
@@ -160,7 +181,7 @@ Choice choose_kernel(int64_t M, int64_t N, int64_t K, int q, int kind, bool alig
   const int64_t named = c.exact ? exact_bytes : M <= kSkinnyMaxM ? split_layout_bytes(M, N, K) : (int64_t)gemm_workspace_bytes(M, N, K);
   const int64_t room = named > 0 && have >= named ? named : 0;
   c.kernel = c.exact ? kRouteExact : kRouteRounded;
-  if (blocked_is_faster(M, N, K, q, kind, c.exact, room > 0)) {
+  if (blocked_is_faster(M, N, K, group, q, kind, c.exact, room > 0)) {
     c.kernel = c.exact ? kRouteStat : kRouteSplit;
     return c;
   }
@@ -181,8 +202,8 @@ Choice choose_kernel(int64_t M, int64_t N, int64_t K, int q, int kind, bool alig
 
 }  // namespace
 
-Route stream_route(int64_t M, int64_t N, int64_t K, int q, int kind, bool aligned, int64_t workspace_bytes) {
-  const Choice c = choose_kernel(M, N, K, q, kind, aligned, workspace_bytes);
+Route stream_route(int64_t M, int64_t N, int64_t K, int group, int q, int kind, bool aligned, int64_t workspace_bytes) {
+  const Choice c = choose_kernel(M, N, K, group, q, kind, aligned, workspace_bytes);
   switch (c.kernel) {
     case kRouteStat: case kRouteSplit: return skinny_route(M, N, K, q, c.exact);
     case kRouteGemm: return gemm_route(M, N, K, q, workspace_bytes);
@@ -196,7 +217,7 @@ hipError_t launch_stream_bf16(const uint16_t* x, int64_t M, const uint8_t* codes
                               size_t workspace_bytes, hipStream_t stream) {
   if (M < 3 || M > kStreamMaxM) return hipErrorInvalidValue;
   const bool aligned = reinterpret_cast<uintptr_t>(scales) % 16 == 0 && reinterpret_cast<uintptr_t>(meta.ptr) % 16 == 0;
-  const Choice c = choose_kernel(M, N, K, q, meta.kind, aligned, workspace != nullptr ? (int64_t)workspace_bytes : 0);
+  const Choice c = choose_kernel(M, N, K, group, q, meta.kind, aligned, workspace != nullptr ? (int64_t)workspace_bytes : 0);
   switch (c.kernel) {
     case kRouteStat: case kRouteSplit:
       return launch_skinny_bf16(x, M, codes, scales, meta, N, K, group, q, y, workspace, c.exact, stream);

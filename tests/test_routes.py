@@ -61,3 +61,16 @@ def test_q8_shapes_run_what_their_comments_say(shapes, kernels):
         for q in (2, 3, 4):
             r = route(M, N, K, 32, q, O.SIGNED_SYM, q8=True)
             assert (r.kernel if r.kernel == "q8_gemv" else f"{r.kernel} {r.tokens}x{r.rows}") == want, (M, N, K, q)
+
+
+@pytest.mark.parametrize("N,K,group,mode,kernel", [
+    (20480, 5120, 32, O.SIGNED_SYM, "rounded"), (19456, 5632, 32, O.SIGNED_SYM, "split"),
+    (24576, 3072, 32, O.SIGNED_SYM, "rounded"), (24576, 4096, 32, O.SIGNED_SYM, "split"),
+    (28672, 2048, 32, O.SIGNED_SYM, "split"), (28672, 4096, 32, O.ASYM, "split"),
+    (16448, 8192, 32, O.ASYM, "rounded"), (18432, 12288, 32, O.ASYM, "split"),
+    (24576, 6144, 32, O.ASYM_MIN, "rounded"), (24576, 4096, 32, O.ASYM, "split"),
+    (20480, 6144, 64, O.ASYM, "rounded"), (24576, 4096, 64, O.ASYM, "split"), (16448, 8192, 128, O.ASYM, "split"),
+])
+@pytest.mark.parametrize("M", [17, 24, 32])
+def test_three_bit_rule_follows_its_measurements(M, N, K, group, mode, kernel):
+    assert route(M, N, K, group, 3, mode, True).kernel == kernel
