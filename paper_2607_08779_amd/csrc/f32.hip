@@ -259,12 +259,19 @@ __global__ __launch_bounds__(256) void matmul_f32_rows_kernel(
 // Short matrices at 1 to 3 tokens take the rows kernel: 2 x 1024 x 4096 runs in 6.8 us
 // against 8.6, 3 x 333 x 1056 in 4.8 against 5.7, 2 x 8 x 32768 in 31 against 47; from M N =
 // 4096 on it loses (1 x 4096 x 4096: 12.1 us against 9.8; 4 x 32 x 4096: 10.0 against 8.2).
+// One token of more than 4096 rows, a second round of the kernel above (its 16 wavefronts fill a
+// CU), takes it too, unless rows are short enough for two workgroups a CU or the rounds are
+// many: 4219x8192 21.0 us against 27.3, 5943x4096 14.4 / 18.9, 8842x3840 19.5 / 24.0, 13956x3840
+// 28.1 / 36.5, but 4009x512 5.5 / 4.0, 6967x896 9.4 / 6.8, 16252x3456 31.8 / 29.5.
 constexpr int64_t kRowsMaxTokens = 3, kRowsMaxOutputs = 3072;
+bool rows_kernel(int64_t M, int64_t N, int64_t K) {
+  return M <= kRowsMaxTokens && (M * N <= kRowsMaxOutputs || (M == 1 && N > 4096 && N <= 15360 && K > 1152));
+}
 
 template <int Q, int META>
 hipError_t f32_dispatch(const float* x, int64_t M, const uint8_t* codes, const uint16_t* scales, const void* meta,
                         int64_t N, int64_t K, int gshift, float* y, hipStream_t stream) {
-  if (M <= kRowsMaxTokens && M * N <= kRowsMaxOutputs) {
+  if (rows_kernel(M, N, K)) {
     matmul_f32_rows_kernel<Q, META><<<dim3((unsigned)((N + 3) / 4)), 256, 0, stream>>>(x, (int)M, codes, scales, meta,
                                                                                      (int)N, (int)K, gshift, y);
     return hipGetLastError();

@@ -605,6 +605,7 @@ def test_gemv_two_tokens_full_size(mode):
 @pytest.mark.parametrize("M,N,K", [
     (1, 3073, 96),      # past the short-matrix kernel: one super-block of three blocks, ragged rows
     (3, 1024, 544),     # its largest three-token matrix
+    (1, 4219, 1184),    # its one token past the 4096 rows of a round
     (4, 17, 32),        # one block: one wavefront, three tokens and a row past the tile's 16
     (8, 40, 4256),      # 34 super-blocks over 16 wavefronts (three steps for two of them)
     (9, 33, 2208),      # 16-token stages, 18 super-blocks over 8 wavefronts
