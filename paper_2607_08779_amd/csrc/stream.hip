@@ -122,13 +122,24 @@ bool three_bits_stream(int64_t tiles, int64_t K, int64_t weights, int group, int
 //     13312x12288 30.7 / 31.0); at 17 to 32 tokens from 1.2e8 on, 3-bit codes excepted:
 //     32 tokens on 10240x12288 31.6 / 35.6, W2 27.9 / 32.8, W3 40.9 / 41.4, but 13312x8192
 //     31.5 / 31.9; two-bit codes on 16384x12288 the other way, 38.2 / 35.4;
+//   513 to 590 tiles, rounded (three row tiles on at most 77 % of the CUs), above 16 tokens from 9e7
+//     weights on: 18 on W2 8320x13312 30.1 / 36.8, 24 on W4 8411x10752 25.4 / 30.2; below from 1.5e8
+//     on: 9 on W3 8768x18304 39.7 / 45.8;
+//   exact with zero points or minimums, whose groups the streaming kernel reads block by block: from
+//     6e7 weights on in groups of 64 and 128 (9 tokens, W2 7296x19456 21.0 / 29.3, 16 on W4
+//     16704x6144 23.8 / 30.7, 7 on 5120x14336 17.1 / 19.3; at 4e7 to 6e7 as often the other way,
+//     0.82 to 1.17), from 8.5e7 on in groups of 32 (W2 23808x5632 21.6 / 27.2, 6251x25600 27.2 /
+//     33.4, W4 16640x9728 32.6 / 41.6), W4 over 512 tiles (up to 512 0.97 to 1.10);
 //   exact over a K of one slice (no workspace needed): over 1024 tiles, and from 512 on
 //     where groups hold a minimum or zero point: 12 tokens on 28672x2048 10.8 / 13.9,
 //     W4 asymmetric on 8192x2048 6.1 / 6.8.
 bool blocked_is_faster(int64_t M, int64_t N, int64_t K, int group, int q, int kind, bool exact, bool workspace) {
   const int64_t tiles = (N + 15) / 16, weights = N * K;
   if (exact && K <= 2048) return tiles > 1024 || (kind != 0 && K > 1024 && tiles >= 512);
-  if (!workspace || M > kSkinnyMaxM || tiles <= 512) return false;
+  if (!workspace || M > kSkinnyMaxM) return false;
+  if (exact && kind != 0 && (group >= 64 ? weights >= 60000000 : weights >= 85000000 && (q == 2 || tiles > 512))) return true;
+  if (tiles <= 512) return false;
+  if (!exact && tiles <= 590 && weights >= (M > 16 ? 90000000 : 150000000)) return true;
   if (tiles > 1024) return exact ? weights >= 150000000 : !(q == 3 && M > 16 && three_bits_stream(tiles, K, weights, group, kind));
   if (M > 16 && q != 3 && weights >= 120000000) return q == 4 || tiles < 900;
   return weights >= 190000000 && !(M > 16 && tiles >= 900) && !(q == 2 && tiles >= 900);
@@ -140,6 +151,10 @@ bool blocked_is_faster(int64_t M, int64_t N, int64_t K, int group, int q, int ki
 //     44.5, and from 1.9e8 weights on 34 tokens on 10240x23168 73.4 / 89.2 (but 10240x8192
 //     34.1 / 31.5); W4, 64 tokens on 20480x10240 92.5 / 97.3; 80 tokens on 20480x1536 W2
 //     17.4 / 23.6, W3 23.6 / 26.8, W4 19.7 / 22.0;
+//   over 1024 tiles of short rows, whose second round is all start: 64 tokens W4 on 24896x512 10.2 /
+//     19.0, 43 on 28189x1024 14.2 / 18.3, 39 on 29707x1408 18.2 / 21.9 (1792 22.5 / 21.8); up to 48
+//     tokens W2 and W3 to K = 896: 41 tokens W2 on 26432x512 9.9 / 16.3, 37 W3 on 22244x896 16.1 /
+//     18.3 (but 43 W3 on 19389x1024 15.7 / 13.6), above 48 to 1536: 49 W3 on 25796x1408 23.4 / 25.0;
 //   over 64 tokens: W2 in several rounds, 28672x4096 41.1 / 44.8 (16384x4096 28.1 / 23.7);
 //     W4 where LDS has no room for four row tiles, from 1.9e8 weights on: 16384x12288
 //     89.8 / 98.5 (but 16384x4096 41.8 / 34.2); below K = 1024 W2 and W4: 16384x576 9.7 /
@@ -147,6 +162,7 @@ bool blocked_is_faster(int64_t M, int64_t N, int64_t K, int group, int q, int ki
 bool tiled_is_faster(int64_t M, int64_t N, int64_t K, int q, int kind) {
   const int64_t tiles = (N + 15) / 16, weights = N * K;
   if (M <= kSkinnyMaxM || tiles <= 512) return false;
+  if (tiles > 1024 && K <= (q == 4 || M > 48 ? 1536 : 896)) return true;
   const int64_t whole = (tiles + 1023) / 1024 * 1024;
   const bool part_filled = 10 * tiles <= 7 * whole;
   if (part_filled) {

@@ -74,3 +74,20 @@ def test_q8_shapes_run_what_their_comments_say(shapes, kernels):
 @pytest.mark.parametrize("M", [17, 24, 32])
 def test_three_bit_rule_follows_its_measurements(M, N, K, group, mode, kernel):
     assert route(M, N, K, group, 3, mode, True).kernel == kernel
+
+
+# Either side of the lines between kernels, where the rules name measured sizes.
+@pytest.mark.parametrize("M,N,K,group,q,mode,kernel", [
+    # short rows over 1024 row tiles: the GEMM above 32 tokens
+    (64, 24896, 512, 64, 4, O.ASYM, "gemm"), (39, 29707, 1408, 32, 4, O.SIGNED_SYM, "gemm"), (43, 23004, 1792, 32, 4, O.ASYM, "rounded"),
+    (41, 26432, 512, 32, 2, O.ASYM, "gemm"), (43, 19389, 1024, 32, 3, O.SIGNED_SYM, "rounded"), (49, 25796, 1408, 32, 3, O.ASYM, "gemm"),
+    # just over 512 row tiles, rounded weights
+    (18, 8320, 13312, 32, 2, O.ASYM_MIN, "split"), (24, 8411, 10752, 32, 4, O.SIGNED_SYM, "split"), (24, 8411, 9216, 32, 4, O.SIGNED_SYM, "rounded"),
+    (9, 8768, 18304, 128, 3, O.SIGNED_SYM, "split"), (9, 8768, 16384, 128, 3, O.SIGNED_SYM, "rounded"),
+    # exact weights with metadata
+    (9, 7296, 19456, 128, 2, O.ASYM, "stat"), (16, 16704, 6144, 128, 4, O.ASYM, "stat"), (7, 5120, 14336, 64, 4, O.ASYM, "stat"),
+    (9, 2048, 24576, 64, 4, O.ASYM, "exact"), (9, 6256, 25600, 32, 2, O.ASYM, "stat"), (9, 6256, 15360, 32, 4, O.ASYM, "exact"),
+    (9, 16640, 9728, 32, 4, O.ASYM_MIN, "stat"), (9, 7296, 19456, 128, 4, O.SIGNED_SYM, "exact"),
+])
+def test_streaming_rules_follow_their_measurements(M, N, K, group, q, mode, kernel):
+    assert route(M, N, K, group, q, mode, True).kernel == kernel
