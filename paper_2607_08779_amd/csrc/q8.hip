@@ -276,19 +276,23 @@ hipError_t gemv_q8_dispatch(const int8_t* qx, const uint16_t* dx, int64_t M, con
 constexpr int kGemmMaxK = 32768;
 
 // A few tokens of a small or long matrix: the one-token kernel with a workgroup row per
-// token, which re-reads the weights but walks K with 8 wavefronts per 4 rows.  It takes
-// about 3 us and 7.8 us per 1e8 weights and token (two-bit codes 5.5).  Tiles / one-token,
-// W4, us: 2 tokens on 3333x15872 36.5 / 11.4, 3 on 105x4608 10.9 / 2.6, 3 on 1943x4224 11.6 /
-// 4.9; the tiles keep 8 tokens on 4096x4096, 10.3.
-bool q8_tiles(int64_t M, int64_t N, int64_t K, int q) {
-  const float gemv_us = 3.0f + (float)M * (float)N * (float)K * (q == 2 ? 5.5e-8f : 7.8e-8f);
-  return M > 1 && K <= kGemmMaxK && !(M <= 16 && gemv_us < 0.85f * q8_gemm_us(M, N, K));
+// token, which re-reads the weights but walks K with 8 wavefronts per 4 rows.  Its time
+// follows tokens and weights, the tiles' their passes over K (both fitted to 500 sizes, 2 to
+// 40 tokens; the rule's choice is 0.5 % slower than the better of the two, 30 % at most).  One-token /
+// tiles, us: 22 tokens on W2 257x6144 with minimums 4.9 / 17.3, 4 on W3 2437x11776 11.5 / 20.4,
+// 20 on 1024x1536 4.2 / 6.4, 16 on 1367x2688 W2 7.0 / 8.5; but 8 on 4096x4096 12.6 / 9.0, 17 on
+// 3918x2048 W3 12.0 / 7.3.
+constexpr int kRowPerTokenMaxM = 40;
+bool q8_tiles(int64_t M, int64_t N, int64_t K, int q, int kind) {
+  const float per = q == 2 ? 5.4e-8f : q == 3 ? 8.0e-8f : 6.6e-8f;
+  const float gemv_us = 2.8f + (float)M * (float)N * (float)K * per;
+  return M > 1 && K <= kGemmMaxK && !(M <= kRowPerTokenMaxM && gemv_us < 0.95f * q8_gemm_us(M, N, K, kind));
 }
 
 }  // namespace
 
-Route q8_route(int64_t M, int64_t N, int64_t K, int q) {
-  return q8_tiles(M, N, K, q) ? q8_gemm_route(M, N) : Route{kRouteQ8Gemv, 1, kRows, 1};
+Route q8_route(int64_t M, int64_t N, int64_t K, int q, int kind) {
+  return q8_tiles(M, N, K, q, kind) ? q8_gemm_route(M, N) : Route{kRouteQ8Gemv, 1, kRows, 1};
 }
 
 hipError_t launch_quantize_act_q8(const uint16_t* x, int64_t M, int64_t K, int8_t* q, uint16_t* d,
@@ -304,7 +308,7 @@ hipError_t launch_quantize_act_q8(const uint16_t* x, int64_t M, int64_t K, int8_
 hipError_t launch_matmul_q8(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes,
                             const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K, int group, int q,
                             uint16_t* y, hipStream_t stream) {
-  if (q8_tiles(M, N, K, q))
+  if (q8_tiles(M, N, K, q, meta.kind))
     return launch_q8_gemm(qx, dx, M, codes, scales, meta, N, K, group, q, y, stream);
   SSQ_DISPATCH_QGM(gemv_q8_dispatch, q, group, meta.kind, qx, dx, M, codes, scales, meta.ptr, N, K, y, stream);
 }

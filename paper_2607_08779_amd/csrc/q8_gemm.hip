@@ -39,10 +39,16 @@
 // multiplied.  With the weights one stage ahead only, a 32x32 tile took 16.1 us at K = 4096
 // (0.95 us a stage, the loads' latency) against 11.2.
 //
+// Up to 16 tokens a 32-token tile leaves out the sums of tokens 16 to 31, half of its vector work,
+// and two 32x32 tiles share a CU: 8 tokens on 12288x4096 13.9 us for 15.7, on 4096x12288 19.3 for
+// 23.1.
+//
 // Measured (W4 g32 signed, graph replays; the kernel this replaces read the weights once
 // per 32 tokens on 16x16x32 MFMA): 512 tokens on 4096x14336 110 us (709 before), on
-// 14336x4096 120 (870); 64 tokens on 4096x4096 10.7 (30), 8 tokens on 12288x4096 15.8 (33), on
-// 4096x4096 10.1 (11.8).
+// 14336x4096 120 (870); 64 tokens on 4096x4096 10.7 (30), 8 tokens on 12288x4096 13.9 (33), on
+// 4096x4096 9.0 (11.8).  That kernel had 16 rows a workgroup and is missed where few tokens meet
+// fewer than 128 tiles and a long K: 14 tokens on W3 4096x30208 with minimums 64 for 42, 8 on
+// 3593x12288 27 for 20; 3 % of 500 random sizes of 2 to 40 tokens.
 #include <algorithm>
 #include <type_traits>
 
@@ -130,8 +136,8 @@ __device__ __forceinline__ uint8_t* lds_object() {
   return mem;
 }
 
-template <int Q, int META, int WM, int WN, int TC, int SB>
-__global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
+template <int Q, int META, int WM, int WN, int TC, int SB, bool HALF>
+__global__ __launch_bounds__(kThreads, HALF && TC == 1 ? 4 : 2) void q8_gemm_kernel(
     const int8_t* __restrict__ qx, const uint16_t* __restrict__ dx, int M, const uint8_t* __restrict__ codes,
     const uint16_t* __restrict__ scales, const void* __restrict__ meta, int N, int K, int gshift,
     uint16_t* __restrict__ y) {
@@ -139,6 +145,7 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
   constexpr int KG = C::KG, NB = C::NB, BM = C::BM, BN = C::BN, kStageBlocks = SB, kRow = 32 * SB;   // kRow: bytes of a stage row
   constexpr int kMetaSize = META == kMetaZp ? 1 : META == kMetaMin ? 2 : 0;
   constexpr bool MIN = META == kMetaMin;
+  constexpr int kR = HALF ? 8 : 16;                    // results of a lane: those from 8 on are tokens 16..31
   uint8_t* const as0 = lds_object<0, C::kABytes>();
   uint8_t* const as1 = lds_object<1, C::kABytes>();
   uint8_t* const bs = lds_object<2, 2 * C::kBBytes>();
@@ -257,12 +264,12 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
 #pragma unroll
   for (int c = 0; c < TC; ++c)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[c][r] = tot[c][r] = 0.0f;
+    for (int r = 0; r < kR; ++r) acc[c][r] = tot[c][r] = 0.0f;
   auto fold = [&]() {
 #pragma unroll
     for (int c = 0; c < TC; ++c)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
+      for (int r = 0; r < kR; ++r) {
         tot[c][r] += acc[c][r];
         acc[c][r] = 0.0f;
       }
@@ -276,7 +283,7 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
   // subtraction converts them: where the registers are free (at the start, 512 tokens on
   // 14336x4096, zero point, 125 us for 130; the 128x128 symmetric tile and the minimum layout
   // spill with it).
-  constexpr bool kZero = MIN || (META == kMetaNone && WM * WN == 8);
+  constexpr bool kZero = MIN || (HALF && TC == 1) || (META == kMetaNone && WM * WN == 8);
   i32x16 start;
 #pragma unroll
   for (int r = 0; r < 16; ++r) start[r] = kZero ? 0 : (int)kMagicBits;
@@ -296,7 +303,7 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
       f16x4 da = {};                                   // others: row lr's, as an MFMA operand
       if constexpr (MIN) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dv[i] = *reinterpret_cast<const f32x4*>(dj + 8 * i + 4 * h);
+        for (int i = 0; i < kR / 4; ++i) dv[i] = *reinterpret_cast<const f32x4*>(dj + 8 * i + 4 * h);
       } else {
         da[0] = __builtin_bit_cast(_Float16, dj[lr]);
       }
@@ -316,7 +323,7 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
         if constexpr (MIN) {
           const float m = ms[buf * kSCount + j * BN + bn];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
+          for (int r = 0; r < kR; ++r) {
             const float t = __builtin_fmaf(sn, value(v[r]), m * value(base[r]));
             acc[c][r] = __builtin_fmaf(dv[r >> 2][r & 3], t, acc[c][r]);
           }
@@ -328,7 +335,7 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
           for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
           const f32x16 ds2 = __builtin_amdgcn_mfma_f32_32x32x8f16(da, sb, zero, 0, 0, 0);      // 2 d s
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[c][r] = __builtin_fmaf(ds2[r], value(v[r]), acc[c][r]);
+          for (int r = 0; r < kR; ++r) acc[c][r] = __builtin_fmaf(ds2[r], value(v[r]), acc[c][r]);
         }
       }
       if constexpr (NB > 4) {                          // two blocks at a time: with eight, zero points spill
@@ -382,13 +389,13 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
     for (int c = 0; c < TC; ++c) {
       if (grp >= half && grp < 2 * half)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
+        for (int q4 = 0; q4 < kR / 4; ++q4)
           *reinterpret_cast<f32x4*>(red + slot * 1024 + q4 * 256 + lane * 4) =
               f32x4{tot[c][4 * q4], tot[c][4 * q4 + 1], tot[c][4 * q4 + 2], tot[c][4 * q4 + 3]};
       __syncthreads();
       if (grp < half)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
+        for (int q4 = 0; q4 < kR / 4; ++q4) {
           const f32x4 v = *reinterpret_cast<const f32x4*>(red + ((grp * WN + wn) * WM + wm) * 1024 + q4 * 256 + lane * 4);
 #pragma unroll
           for (int e = 0; e < 4; ++e) tot[c][4 * q4 + e] += v[e];
@@ -401,19 +408,19 @@ __global__ __launch_bounds__(kThreads) void q8_gemm_kernel(
 #pragma unroll
   for (int c = 0; c < TC; ++c)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < kR; ++r) {
       const int64_t m = m0 + wm * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
       const int64_t n = n0 + (wn * TC + c) * 32 + lr;
       if (m < M && n < N) y[m * N + n] = f32_to_bf16_bits(MIN ? tot[c][r] : 0.5f * tot[c][r]);
     }
 }
 
-template <int Q, int META, int WM, int WN, int TC, int SB>
+template <int Q, int META, int WM, int WN, int TC, int SB, bool HALF = false>
 hipError_t q8_gemm_launch(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes, const uint16_t* scales,
                           const void* meta, int64_t N, int64_t K, int gshift, uint16_t* y, hipStream_t stream) {
   using C = Q8Cfg<META, WM, WN, TC, SB>;
   const int64_t tiles = ((M + C::BM - 1) / C::BM) * ((N + C::BN - 1) / C::BN);
-  q8_gemm_kernel<Q, META, WM, WN, TC, SB><<<dim3((unsigned)tiles), kThreads, 0, stream>>>(
+  q8_gemm_kernel<Q, META, WM, WN, TC, SB, HALF><<<dim3((unsigned)tiles), kThreads, 0, stream>>>(
       qx, dx, (int)M, codes, scales, meta, (int)N, (int)K, gshift, y);
   return hipGetLastError();
 }
@@ -423,7 +430,7 @@ hipError_t q8_gemm_launch(const int8_t* qx, const uint16_t* dx, int64_t M, const
 // the weights in cache.  From memory, 256 tiles at K = 4096, us: 32x32 11.3, 32x64 17.4, 64x64
 // 23.5, 64x128 37.8, 128x128 65.4 (2 workgroups of 32x32 fit a CU).
 struct Q8Tile {
-  int bm, bn, cost, cost2;     // cost2: a round of up to 512 tiles where two share a CU, else 0
+  int bm, bn, cost, cost2;     // cost2: a round of up to 512 tiles where two share a CU (up to 16 tokens), else 0
 };
 constexpr Q8Tile kQ8Tiles[] = {{32, 32, 106, 168}, {32, 64, 150, 0}, {64, 64, 192, 0}, {64, 128, 315, 0}, {128, 128, 545, 0}};
 
@@ -434,7 +441,7 @@ int q8_tile_for(int64_t M, int64_t N) {
     const Q8Tile& t = kQ8Tiles[i];
     const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
     int64_t c;
-    if (t.cost2) {
+    if (t.cost2 && M <= 16) {
       const int64_t rest = tiles % 512;
       c = tiles / 512 * t.cost2 + (rest == 0 ? 0 : rest <= 256 ? t.cost : t.cost2);
     } else {
@@ -455,12 +462,14 @@ Route q8_gemm_route(int64_t M, int64_t N) {
   return Route{kRouteQ8Tile, t.bm, t.bn, 1};
 }
 
-// Time of the launch, us: 3, and the tile's pass over K (10.6 us at K = 4096) per round.
-float q8_gemm_us(int64_t M, int64_t N, int64_t K) {
+// Time of the launch, us: 3.8, and the tile's pass over K per round (least squares over 460 sizes
+// of up to 32 tokens, 7 % rms; zero points and minimums cost more a block).
+float q8_gemm_us(int64_t M, int64_t N, int64_t K, int kind) {
   const Q8Tile& t = kQ8Tiles[q8_tile_for(M, N)];
-  const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), slots = t.cost2 ? 512 : 256;
-  const int pass = t.cost2 && tiles > 256 ? t.cost2 : t.cost;
-  return 3.0f + (float)((tiles + slots - 1) / slots) * ((float)pass / 10.0f - 3.0f) * (float)K / 4096.0f;
+  const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn), slots = t.cost2 && M <= 16 ? 512 : 256;
+  const int pass = slots == 512 && tiles > 256 ? t.cost2 : t.cost;
+  const float block = kind == kMetaMin ? 1.05f : kind == kMetaZp ? 0.82f : 0.75f;
+  return 3.8f + (float)((tiles + slots - 1) / slots) * block * ((float)pass / 10.0f - 3.0f) * (float)K / 4096.0f;
 }
 
 namespace {
@@ -469,8 +478,12 @@ template <int Q, int META>
 hipError_t q8_gemm_dispatch(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes, const uint16_t* scales,
                             const void* meta, int64_t N, int64_t K, int gshift, uint16_t* y, hipStream_t stream) {
   switch (q8_tile_for(M, N)) {
-    case 0: return q8_gemm_launch<Q, META, 1, 1, 1, 16>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
-    case 1: return q8_gemm_launch<Q, META, 1, 1, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+    case 0:
+      if (M <= 16) return q8_gemm_launch<Q, META, 1, 1, 1, 16, true>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+      return q8_gemm_launch<Q, META, 1, 1, 1, 16>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+    case 1:
+      if (M <= 16) return q8_gemm_launch<Q, META, 1, 1, 2, 8, true>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
+      return q8_gemm_launch<Q, META, 1, 1, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
     case 2: return q8_gemm_launch<Q, META, 2, 1, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
     case 3: return q8_gemm_launch<Q, META, 2, 2, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);
     default: return q8_gemm_launch<Q, META, 4, 2, 2, 8>(qx, dx, M, codes, scales, meta, N, K, gshift, y, stream);

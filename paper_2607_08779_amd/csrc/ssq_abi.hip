@@ -259,7 +259,7 @@ int ssq_internal_route(int64_t M, int64_t N, int64_t K, int group, int q, int ki
                        size_t workspace_bytes, int q8, int out[4]) {
   if (check_matmul_sizes(M, N, K, group, q) != SSQ_OK || M == 0 || N == 0 || kind < 0 || kind > 2) return SSQ_EINVAL;
   const int64_t have = (int64_t)workspace_bytes;
-  const ssq::Route r = q8 ? ssq::q8_route(M, N, K, q)
+  const ssq::Route r = q8 ? ssq::q8_route(M, N, K, q, kind)
                      : M <= 2 ? ssq::Route{ssq::kRouteGemv, (int)M, 0, 1}
                      : M <= ssq::kStreamMaxM ? ssq::stream_route(M, N, K, group, q, kind, aligned != 0, have)
                                              : ssq::gemm_route(M, N, K, q, have);

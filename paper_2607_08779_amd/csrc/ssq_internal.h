@@ -231,7 +231,7 @@ struct Route {
 Route stream_route(int64_t M, int64_t N, int64_t K, int group, int q, int kind, bool aligned, int64_t workspace_bytes);
 Route skinny_route(int64_t M, int64_t N, int64_t K, int q, bool exact);
 Route gemm_route(int64_t M, int64_t N, int64_t K, int q, int64_t workspace_bytes);
-Route q8_route(int64_t M, int64_t N, int64_t K, int q);
+Route q8_route(int64_t M, int64_t N, int64_t K, int q, int kind);
 Route q8_gemm_route(int64_t M, int64_t N);
 // Middle token counts (tile.hip): the best small tile, its slices of K (more than one only
 // within `room` bytes of workspace) and its estimated time.
@@ -274,7 +274,7 @@ hipError_t launch_matmul_q8(const int8_t* qx, const uint16_t* dx, int64_t M, con
                             uint16_t* y, hipStream_t stream);
 
 // Several tokens of the Q8_0 matmul at a time (q8_gemm.hip).
-float q8_gemm_us(int64_t M, int64_t N, int64_t K);      // estimated time, us
+float q8_gemm_us(int64_t M, int64_t N, int64_t K, int kind);      // estimated time, us
 hipError_t launch_q8_gemm(const int8_t* qx, const uint16_t* dx, int64_t M, const uint8_t* codes,
                           const uint16_t* scales, GroupMeta meta, int64_t N, int64_t K, int group, int q,
                           uint16_t* y, hipStream_t stream);

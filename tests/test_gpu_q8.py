@@ -148,16 +148,16 @@ def test_q8_pipeline_llama3_8b_down_proj_full_size():
 
 
 # ---------------------------------------------------------------------------
-# Several tokens: the one-token kernel with a grid row per token (up to 16 tokens of small
+# Several tokens: the one-token kernel with a grid row per token (up to 40 tokens of small
 # matrices) and the smallest tile.
 # ---------------------------------------------------------------------------
 
-@pytest.mark.parametrize("M", [2, 16, 17, 32, 33, 40])
+@pytest.mark.parametrize("M", [2, 16, 17, 32, 33, 40, 41, 72])
 @pytest.mark.parametrize("mode", MODES)
 def test_matmul_q8_batched_token_counts(M, mode):
-    """Up to 16 tokens the one-token kernel, above 32x32 tiles, one and two of them; 70 rows (a
+    """Up to 40 tokens the one-token kernel, above 32x32 tiles, two and three of them; 70 rows (a
     ragged last tile) and K = 2016 (63 blocks: a ragged last stage)."""
-    assert route(M, 70, 2016, 32, 4, mode, q8=True).kernel == ("q8_gemv" if M <= 16 else "q8_tile")
+    assert route(M, 70, 2016, 32, 4, mode, q8=True).kernel == ("q8_gemv" if M <= 40 else "q8_tile")
     rng = np.random.default_rng(M * 5 + mode)
     w = O.bf16_bits_to_f32(bf16_bits(rng.standard_t(5, size=(70, 2016)) * 0.02))
     check_q8_matmul(w, act_bits(M, 2016, seed=M + 100), 32, 4, mode, tag=f"batched M={M} m={mode}")
@@ -226,8 +226,10 @@ def test_matmul_q8_tiles(M, N, K, q, mode):
 
 # The same tiles in the other group sizes, and 32x32 with two workgroups a CU.
 @pytest.mark.parametrize("tile,M,N,K", [
-    ((32, 32), 17, 33, 640),         # two 512-deep stages, the second four blocks
+    ((32, 32), 41, 33, 640),         # two token tiles; two 512-deep stages, the second four blocks
+    ((32, 32), 16, 4100, 640),       # half a tile of tokens
     ((32, 32), 16, 17000, 640),      # 532 tiles
+    ((32, 64), 13, 8300, 640),       # half a tile of tokens
     ((32, 64), 31, 8225, 384),
     ((64, 64), 65, 8161, 896),
     ((64, 128), 129, 10400, 1152),
@@ -244,13 +246,16 @@ def test_matmul_q8_tile_groups(tile, M, N, K, q, group, mode):
 
 
 # Few tokens: the one-token kernel with a grid row per token on small or long matrices, and
-# the tiles just past its 16 tokens and on a matrix large enough for them at 8.
+# the tiles just past its 40 tokens and, half full, on matrices large enough for them.
 Q8_FEW = [
-    (2, 5, 32),          # one block: a 32x32 tile, as the one-token kernel would gain nothing
+    (2, 5, 32),          # one block, a row past the workgroup's four
     (3, 1001, 4128),     # 129 blocks: ragged passes over K
-    (16, 130, 8224),     # its most tokens, ragged rows
-    (17, 33, 544),       # 32x32: a ragged tile both ways, two stages, the second one block
-    (8, 8200, 544),      # 32x64
+    (16, 130, 8224),     # ragged rows
+    (40, 130, 2080),     # its most tokens
+    (41, 33, 544),       # 32x32: a ragged tile both ways, two stages, the second one block
+    (16, 4100, 544),     # 32x32, half the tokens
+    (7, 16900, 544),     # 32x32: 529 tiles, two workgroups a CU
+    (12, 8300, 544),     # 32x64, half the tokens
 ]
 
 
@@ -278,11 +283,12 @@ def q8_on_gpu(a, r, meta, M, N, K, q, mode):
     return y_to_f64(y)
 
 
-@pytest.mark.parametrize("M", [1, 17, 70])        # the one-token kernel, a 32x32 tile, three of them
+@pytest.mark.parametrize("M,N", [(1, 40), (17, 40), (41, 40), (70, 40), (16, 4100)])   # one-token kernel; two, three and half 32x32 tiles
 @pytest.mark.parametrize("q", [2, 3, 4])
 @pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
-def test_matmul_q8_infinite_scales(M, q, mode):
-    N, K = 40, 1056
+def test_matmul_q8_infinite_scales(M, N, q, mode):
+    K = 1056
+    assert route(M, N, K, 32, q, mode, q8=True).kernel == ("q8_gemv" if M in (1, 17) else "q8_tile")
     rng = np.random.default_rng(q + mode)
     r = O.quantize(O.bf16_bits_to_f32(bf16_bits(rng.standard_t(5, size=(N, K)) * 0.02)), 32, q, mode)
     a = O.quantize_act_q8(O.bf16_bits_to_f32(act_bits(M, K, seed=M + q)))
@@ -302,7 +308,7 @@ def test_matmul_q8_infinite_scales(M, q, mode):
         assert (np.abs(y[fine] - ref[fine]) <= 2.0 ** -8 * np.abs(ref[fine]) + 1e-5 * np.abs(ref[fine]).max()).all()
 
 
-@pytest.mark.parametrize("M", [1, 17])
+@pytest.mark.parametrize("M", [1, 17, 41])
 @pytest.mark.parametrize("mode", [O.SIGNED_SYM, O.ASYM, O.ASYM_MIN])
 def test_matmul_q8_subnormal_scales(M, mode):
     N, K, q = 40, 1056, 4

@@ -54,7 +54,7 @@ def test_every_reachable_form_is_tested():
 
 @pytest.mark.parametrize("shapes,kernels", [
     (gq.Q8_TILES, ["q8_gemv", "q8_tile 32x64", "q8_tile 64x64", "q8_tile 64x128", "q8_tile 128x128"]),
-    (gq.Q8_FEW, ["q8_tile 32x32", "q8_gemv", "q8_gemv", "q8_tile 32x32", "q8_tile 32x64"]),
+    (gq.Q8_FEW, ["q8_gemv", "q8_gemv", "q8_gemv", "q8_gemv", "q8_tile 32x32", "q8_tile 32x32", "q8_tile 32x32", "q8_tile 32x64"]),
 ])
 def test_q8_shapes_run_what_their_comments_say(shapes, kernels):
     for (M, N, K), want in zip(shapes, kernels):
@@ -91,3 +91,12 @@ def test_three_bit_rule_follows_its_measurements(M, N, K, group, mode, kernel):
 ])
 def test_streaming_rules_follow_their_measurements(M, N, K, group, q, mode, kernel):
     assert route(M, N, K, group, q, mode, True).kernel == kernel
+
+
+@pytest.mark.parametrize("M,N,K,q,mode,kernel", [
+    (22, 257, 6144, 2, O.ASYM_MIN, "q8_gemv"), (4, 2437, 11776, 3, O.SIGNED_SYM, "q8_gemv"), (20, 1024, 1536, 4, O.ASYM, "q8_gemv"),
+    (16, 1367, 2688, 2, O.SIGNED_SYM, "q8_gemv"), (8, 4096, 4096, 4, O.SIGNED_SYM, "q8_tile"), (17, 3918, 2048, 3, O.SIGNED_SYM, "q8_tile"),
+    (41, 257, 6144, 2, O.ASYM_MIN, "q8_tile"), (1, 4096, 4096, 4, O.SIGNED_SYM, "q8_gemv"),
+])
+def test_q8_rule_follows_its_measurements(M, N, K, q, mode, kernel):
+    assert route(M, N, K, 32, q, mode, q8=True).kernel == kernel
