@@ -120,15 +120,16 @@ int ssq_quantize_f32(const float* W, int64_t rows, int64_t cols, int group, int 
  * each among the tokens through bf16 MFMA: for q = 2 or 4, M <= 16 and K a multiple
  * of 512 (with a workspace, or K <= 2048) the weights enter exactly (the code as
  * 128 + u, the scale and offset applied per 32-weight block in fp32), otherwise each
- * weight is dequantized once and rounded to bf16; larger M (and large matrices from
- * M = 33 on) run a tiled kernel that dequantizes weight tiles into LDS and multiplies
- * them with bf16 MFMA.
+ * weight is dequantized once and rounded to bf16.  From 49 tokens on small tiles (32 x 32
+ * to 128 x 64 outputs, bf16 MFMA) run where they are estimated faster; larger M, and
+ * large matrices or short rows from M = 33 on, run a tiled kernel that dequantizes weights
+ * in registers into its bf16 MFMA operands.
  *
  *   x      device, bf16 bits [M, K] row-major, read only
  *   M      >= 0, number of activation rows (tokens)
  *   codes  device, u8 [N, K*q/8] as written by ssq_quantize
  *   scales device, u16 [N, K/group]
- *   zp     device, u8 [N, K/group] for the asymmetric format, else NULL
+ *   zp     device, u8 [N, K/group] for the asymmetric format (any byte), else NULL
  *   N      >= 0, number of weight rows (outputs)
  *   K      > 0, multiple of group, at most 2^22
  *   group  32, 64 or 128;  q  2, 3 or 4
@@ -145,8 +146,8 @@ int ssq_matmul(const uint16_t* x, int64_t M, const uint8_t* codes, const uint16_
  * blocks of K, so disjoint block ranges can be reduced separately and added).
  * Returns 0 when splitting would not help (M <= 2: the streaming GEMV, or enough
  * output tiles already) or the arguments are invalid.  3 <= M <= 32 sizes the
- * batched-decode kernels' split, larger M the tiled kernel's (which the streaming
- * kernels use a part of).
+ * batched-decode kernels' split, larger M the tiled kernel's (of which the streaming
+ * kernels and the small tiles use a part).
  */
 size_t ssq_matmul_workspace_size(int64_t M, int64_t N, int64_t K, int group, int q);
 
@@ -311,9 +312,12 @@ int ssq_quantize_act_q8(const uint16_t* x, int64_t M, int64_t K, int8_t* q, uint
  *   I = sum_{j in b} qx[m, j] u[n, j],  R = sum_{j in b} qx[m, j]     (exact integers)
  *   y[m, n] += d[m, b] s[n, g] (I - o[n, g] R)
  * with o = 2^(q-1) (zp == NULL: the symmetric formats) or the zero point zp[n, g].
- * Exact integer block terms (4-way byte dot products at M = 1; int8 MFMA, v_mfma_i32_32x32x32_i8,
- * in tiles of 32 to 128 tokens for 2 <= M and K <= 32768; longer rows take the M = 1
- * kernel per token); fp32 accumulation; y rounded to bf16 once.
+ * Exact integer block terms: 4-way byte dot products at M = 1, for K > 32768 and for up to
+ * 40 tokens where that kernel, run per token, is estimated faster (few rows, or few tokens);
+ * else int8 MFMA (v_mfma_i32_32x32x32_i8) in tiles of 32 to 128 tokens.  Products d s and block
+ * terms are rounded once, by the binary32 addition (the minimum layout rounds s I + m R
+ * first); infinite and NaN scales give the same on both kernels.  y is rounded to bf16 once.  With
+ * several tokens a zero point is at most 128.
  *
  *   qx, dx codes and scales from ssq_quantize_act_q8 ([M, K] int8, 16-byte aligned;
  *          [M, K/32] binary16, 2-byte aligned)
