@@ -125,11 +125,11 @@ bool three_bits_stream(int64_t tiles, int64_t K, int64_t weights, int group, int
 //   513 to 590 tiles, rounded (three row tiles on at most 77 % of the CUs), above 16 tokens from 9e7
 //     weights on: 18 on W2 8320x13312 30.1 / 36.8, 24 on W4 8411x10752 25.4 / 30.2; below from 1.5e8
 //     on: 9 on W3 8768x18304 39.7 / 45.8;
-//   exact with zero points or minimums, whose groups the streaming kernel reads block by block: from
-//     6e7 weights on in groups of 64 and 128 (9 tokens, W2 7296x19456 21.0 / 29.3, 16 on W4
-//     16704x6144 23.8 / 30.7, 7 on 5120x14336 17.1 / 19.3; at 4e7 to 6e7 as often the other way,
-//     0.82 to 1.17), from 8.5e7 on in groups of 32 (W2 23808x5632 21.6 / 27.2, 6251x25600 27.2 /
-//     33.4, W4 16640x9728 32.6 / 41.6), W4 over 512 tiles (up to 512 0.97 to 1.10);
+//   exact with zero points or minimums stays here below those sizes, though the others would be
+//     faster from 6e7 weights on in groups of 64 and 128 (9 tokens, W2 7296x19456 21.0 / 29.3, 16
+//     on W4 16704x6144 23.8 / 30.7) and 8.5e7 in groups of 32 (W2 23808x5632 21.6 / 27.2): their
+//     sums cancel the offsets over 16 blocks, not within one, and are ten times as far from 64
+//     bits (5.7e-3 of the bf16 outputs off the correctly rounded one for 5.8e-4);
 //   exact over a K of one slice (no workspace needed): over 1024 tiles, and from 512 on
 //     where groups hold a minimum or zero point: 12 tokens on 28672x2048 10.8 / 13.9,
 //     W4 asymmetric on 8192x2048 6.1 / 6.8.
@@ -137,7 +137,6 @@ bool blocked_is_faster(int64_t M, int64_t N, int64_t K, int group, int q, int ki
   const int64_t tiles = (N + 15) / 16, weights = N * K;
   if (exact && K <= 2048) return tiles > 1024 || (kind != 0 && K > 1024 && tiles >= 512);
   if (!workspace || M > kSkinnyMaxM) return false;
-  if (exact && kind != 0 && (group >= 64 ? weights >= 60000000 : weights >= 85000000 && (q == 2 || tiles > 512))) return true;
   if (tiles <= 512) return false;
   if (!exact && tiles <= 590 && weights >= (M > 16 ? 90000000 : 150000000)) return true;
   if (tiles > 1024) return exact ? weights >= 150000000 : !(q == 3 && M > 16 && three_bits_stream(tiles, K, weights, group, kind));

@@ -84,10 +84,8 @@ def test_three_bit_rule_follows_its_measurements(M, N, K, group, mode, kernel):
     # just over 512 row tiles, rounded weights
     (18, 8320, 13312, 32, 2, O.ASYM_MIN, "split"), (24, 8411, 10752, 32, 4, O.SIGNED_SYM, "split"), (24, 8411, 9216, 32, 4, O.SIGNED_SYM, "rounded"),
     (9, 8768, 18304, 128, 3, O.SIGNED_SYM, "split"), (9, 8768, 16384, 128, 3, O.SIGNED_SYM, "rounded"),
-    # exact weights with metadata
-    (9, 7296, 19456, 128, 2, O.ASYM, "stat"), (16, 16704, 6144, 128, 4, O.ASYM, "stat"), (7, 5120, 14336, 64, 4, O.ASYM, "stat"),
-    (9, 2048, 24576, 64, 4, O.ASYM, "exact"), (9, 6256, 25600, 32, 2, O.ASYM, "stat"), (9, 6256, 15360, 32, 4, O.ASYM, "exact"),
-    (9, 16640, 9728, 32, 4, O.ASYM_MIN, "stat"), (9, 7296, 19456, 128, 4, O.SIGNED_SYM, "exact"),
+    # exact weights with metadata: the streaming kernel's sums are closer
+    (9, 7296, 19456, 128, 2, O.ASYM, "exact"), (16, 16704, 6144, 128, 4, O.ASYM, "exact"), (9, 16640, 9728, 32, 4, O.ASYM_MIN, "stat"),
 ])
 def test_streaming_rules_follow_their_measurements(M, N, K, group, q, mode, kernel):
     assert route(M, N, K, group, q, mode, True).kernel == kernel
